@@ -204,9 +204,9 @@ soax_status soax_step_fused(soax_set* set, int32_t integrator, double dt, int64_
  * Override the launch shape of soax_step for one layout: block threads
  * (64..1024, multiple of 64) and particles per thread (1, 2 or 4; SoA only).
  * 0 restores the default: 128 threads (256 for the AoS layouts) and one
- * particle per thread; for the steps in the ABC field (RK2, Heun, RK4) on SoA
- * arrays that are 16-byte aligned and span at least 128 MB (positions and
- * velocities), 64 threads and two particles per thread.
+ * particle per thread; two particles per thread for RK4 steps on SoA arrays
+ * that are 16-byte aligned and span at least 128 MB (positions and
+ * velocities).
  * Heun and RK4 steps, and any step whose positions or velocities are 8-byte
  * elements, take at most two per thread.  Results do not depend on the
  * shape.
@@ -520,8 +520,8 @@ soax_status soax_copy(void* dst, const void* src, int64_t bytes, void* stream);
 /*
  * Bandwidth probes: the memory accesses of the streaming SoA steps with their
  * arithmetic taken out, on caller-owned device arrays pos[3] (n doubles each)
- * and vel[3] (n floats each), one particle per thread (the RK2 step itself
- * takes two), with the step kernels' buffer windows and cache policies (nt
+ * and vel[3] (n floats each), one particle per thread, with the step kernels'
+ * buffer windows and cache policies (nt
  * loads, sc0 sc1 nt stores).  They measure what the step kernels' access
  * patterns reach on this memory system, as soax_copy does for plain
  * streaming:

@@ -34,6 +34,25 @@ __device__ __forceinline__ double wrap_box(double x) {
   return (x >= kBoxL) ? hi : ((x < 0.0) ? lo : x);
 }
 
+// wrap_box of three coordinates.  Few particles leave the box in a step, so
+// one unsigned comparison of the largest high word (a negative coordinate's
+// sign bit makes it large, as are NaNs and everything from L's own high word
+// up) skips the wrap for the waves in which none did: 2 instructions in place
+// of about 30.  50 fused RK2 steps of 1e7 particles 2.34 -> 2.10 ms, RK4 at
+// 6e6 0.90 -> 0.88 ms per 10 steps, the 256-set batch 3% less.
+__device__ __forceinline__ uint32_t high_word(double x) {
+  return static_cast<uint32_t>(__builtin_bit_cast(uint64_t, x) >> 32);
+}
+
+__device__ __forceinline__ void wrap_box3(double& x, double& y, double& z) {
+  constexpr uint32_t kEdge = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, kBoxL) >> 32);
+  if (__builtin_expect(max(max(high_word(x), high_word(y)), high_word(z)) >= kEdge, 0)) {
+    x = wrap_box(x);
+    y = wrap_box(y);
+    z = wrap_box(z);
+  }
+}
+
 // sin and cos of the three coordinates of a point.
 struct Trig3 {
   double sx, cx, sy, cy, sz, cz;
@@ -44,6 +63,20 @@ __device__ __forceinline__ Trig3 trig3(double x, double y, double z) {
   trig::sincos_fast(x, &t.sx, &t.cx);
   trig::sincos_fast(y, &t.sy, &t.cy);
   trig::sincos_fast(z, &t.sz, &t.cz);
+  return t;
+}
+
+// trig3 with one range check for the three coordinates, so that the three
+// evaluations are one block of straight-line code; the same values.  For
+// steps bound by arithmetic (RK4: 1.5% faster at 1e8); the RK2 step, which
+// waits for each coordinate's load in turn, was 1% slower this way.
+__device__ __forceinline__ Trig3 trig3_joined(double x, double y, double z) {
+  if (__builtin_expect(trig::beyond_fast(x) | trig::beyond_fast(y) | trig::beyond_fast(z), 0))
+    return trig3(x, y, z);
+  Trig3 t;
+  trig::sincos_core(x, &t.sx, &t.cx);
+  trig::sincos_core(y, &t.sy, &t.cy);
+  trig::sincos_core(z, &t.sz, &t.cz);
   return t;
 }
 
@@ -325,7 +358,7 @@ __device__ __forceinline__ void heun_parts(const Abc& p, double dt, double x, do
 template <int TIER>
 __device__ __forceinline__ void rk4_parts(const Abc& p, double dt, double x, double y, double z,
                                           Trig3& t, double& d0, double& d1, double& d2) {
-  t = trig3(x, y, z);
+  t = trig3_joined(x, y, z);
   const double h = 0.5 * dt;
   double k10, k11, k12, k20, k21, k22, k30, k31, k32, k40, k41, k42;
   field_of(p, t, k10, k11, k12);
@@ -376,11 +409,7 @@ __device__ __forceinline__ void update_particle(PT& x0, PT& x1, PT& x2, VT& v0, 
     double y1 = widen(x1) + dt * widen(v1);
     double y2 = widen(x2) + dt * widen(v2);
     if constexpr (std::is_same<PT, double>::value) {
-      if (wrap) {
-        y0 = wrap_box(y0);
-        y1 = wrap_box(y1);
-        y2 = wrap_box(y2);
-      }
+      if (wrap) wrap_box3(y0, y1, y2);
     }
     x0 = static_cast<PT>(y0);
     x1 = static_cast<PT>(y1);
@@ -396,11 +425,7 @@ __device__ __forceinline__ void update_particle(PT& x0, PT& x1, PT& x2, VT& v0, 
     Trig3 t;
     double d0, d1, d2;
     field_step<INTEG, TIER>(p, dt, s0, s1, s2, y0, y1, y2, t, d0, d1, d2);
-    if (wrap) {
-      y0 = wrap_box(y0);
-      y1 = wrap_box(y1);
-      y2 = wrap_box(y2);
-    }
+    if (wrap) wrap_box3(y0, y1, y2);
     x0 = static_cast<PT>(y0);
     x1 = static_cast<PT>(y1);
     x2 = static_cast<PT>(y2);

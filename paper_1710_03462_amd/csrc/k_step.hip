@@ -5,8 +5,8 @@
 // streaming read-modify-write with no reuse inside a step, so the kernels are
 // shaped for HBM, not for the matrix cores:
 //  * SoA: each thread owns `VEC` consecutive particles (one by default; two,
-//    with 16-byte position accesses, for the field integrators on sets that
-//    stream from HBM, where that shape measured fastest), so a wave reads and
+//    with 16-byte position accesses, for RK4 on sets that stream from HBM,
+//    where that shape measured fastest), so a wave reads and
 //    writes each array it touches as one contiguous run; arrays the step does
 //    not use (id, mass, ...) are never read, the SoA advantage of Section 2.
 //  * AoS: a workgroup stages a tile of whole records through LDS with
@@ -324,11 +324,7 @@ __global__ __launch_bounds__(256) void soa_fused_kernel(SoaStepArgs a, int64_t n
       s2 = z;
       double y0, y1, y2;
       field_step<INTEG, TIER>(p, a.dt, s0, s1, s2, y0, y1, y2, t, d0, d1, d2);
-      if (a.wrap) {
-        y0 = wrap_box(y0);
-        y1 = wrap_box(y1);
-        y2 = wrap_box(y2);
-      }
+      if (a.wrap) wrap_box3(y0, y1, y2);
       x = y0;
       y = y1;
       z = y2;
