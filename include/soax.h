@@ -491,7 +491,8 @@ soax_status soax_batch_step(soax_batch* batch, const double* dt, const double* a
  * the current value.  The grid is min(CUs x blocks_per_cu, tiles) workgroups
  * walking the tile list with a grid stride, so a value of at least
  * tiles / CUs gives every tile its own workgroup (the default, with block 256
- * and 1 particle per thread). */
+ * and 1 particle per thread, or 2 for a batch whose positions and velocities
+ * span at least 128 MB). */
 soax_status soax_batch_config(soax_batch* batch, int32_t block, int32_t per_thread,
                               int32_t blocks_per_cu);
 soax_status soax_batch_get_config(const soax_batch* batch, int32_t* block, int32_t* per_thread,

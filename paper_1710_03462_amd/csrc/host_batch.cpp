@@ -26,8 +26,8 @@ struct soax_batch {
   std::vector<uint64_t> generations;  // of each set when the batch was made
   int vel_t = kF32;
   int64_t total = 0;
-  // default: one tile per workgroup (the grid covers every tile), one
-  // particle per thread -- the fastest shape on the uneven 256-set batch
+  // default: one tile per workgroup (the grid covers every tile); particles
+  // per thread by the batch's size (soax_batch_create)
   int block = 256, per_thread = 1, blocks_per_cu = kMaxBlocksPerCu;
   int cus = 256;
   std::string arch;
@@ -225,6 +225,13 @@ soax_status soax_batch_create(soax_set* const* sets, int32_t nsets, soax_batch**
   for (int i = 0; i < nsets; ++i) b->generations.push_back(sets[i]->generation);
   b->vel_t = vel_t;
   b->total = total;
+  // Two consecutive particles per thread (16-byte position accesses) where
+  // the batch streams through HBM, one where it stays in the caches and is
+  // bound by latency.  us per step in workgroups of 256, one / two per thread:
+  // 493 / 470 for 256 sets of 4.6e7 particles in all, 75 / 71 for 100 sets of
+  // 6.8e6 (246 MB), 7.8 / 8.6 for 64 sets of 4e5.
+  if (total * soa_step_bytes(kRk2Abc, sizeof(double), dtype_size(vel_t)) >= kStreamBytes)
+    b->per_thread = 2;
   int dev = 0;
   hipDeviceProp_t prop;
   hipError_t e = hipGetDevice(&dev);
