@@ -134,12 +134,6 @@ __device__ __forceinline__ void rk2_midpoint_parts(const Abc& p, double dt, doub
   z = z + d2;
 }
 
-// The field's amplitudes times s: s u(x) is then one product and one fma
-// per component, like u(x) itself.
-__device__ __forceinline__ Abc scaled(const Abc& p, double s) {
-  return Abc{s * p.A, s * p.B, s * p.C};
-}
-
 // Alignment (bytes) of a run of VEC consecutive T starting at a multiple of
 // VEC elements in a 16-byte aligned array.
 template <typename T, int VEC>

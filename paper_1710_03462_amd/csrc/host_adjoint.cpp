@@ -64,8 +64,8 @@ soax_status soax_rk2_forward_ckpt_strided(const double* const* x0, double* const
   a.n = n;
   a.nsteps = nsteps;
   a.k = k;
-  a.dt = dt;
-  a.abc = AbcParams{abc[0], abc[1], abc[2]};
+  a.step = step_abc(AbcParams{abc[0], abc[1], abc[2]}, dt);
+  a.tier = shift_tier(dt, abc[0], abc[1], abc[2]);
   HIP_TRY(launch_rk2_forward_ckpt(a, as_stream(stream)), "forward launch");
   return SOAX_OK;
 }
@@ -109,7 +109,8 @@ soax_status soax_adjoint_strided(const double* tape, const double* const* lamT, 
   a.nsteps = nsteps;
   a.k = k;
   a.dt = dt;
-  a.abc = AbcParams{abc[0], abc[1], abc[2]};
+  a.step = step_abc(AbcParams{abc[0], abc[1], abc[2]}, dt);
+  a.tier = shift_tier(dt, abc[0], abc[1], abc[2]);
   e = launch_adjoint(a, s);
   hipError_t e2 = hipFreeAsync(partial, s);
   if (e != hipSuccess) return hip_fail(e, "adjoint launch");
@@ -198,7 +199,8 @@ soax_status soax_adjoint_noalloc(const double* tape, const double* const* lamT, 
   a.nsteps = nsteps;
   a.k = k;
   a.dt = dt;
-  a.abc = AbcParams{abc[0], abc[1], abc[2]};
+  a.step = step_abc(AbcParams{abc[0], abc[1], abc[2]}, dt);
+  a.tier = shift_tier(dt, abc[0], abc[1], abc[2]);
   HIP_TRY(launch_adjoint(a, as_stream(stream)), "adjoint launch");
   return SOAX_OK;
 }

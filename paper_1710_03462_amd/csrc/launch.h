@@ -38,6 +38,18 @@ struct AbcParams {
   double A, B, C;
 };
 
+// The amplitudes times dt/2 and dt: (dt/2) u and dt u are the fields of the
+// scaled amplitudes.  Computed on the host so that kernels read them from
+// scalar registers.
+struct StepAbc {
+  AbcParams h, d;
+};
+
+inline StepAbc step_abc(const AbcParams& p, double dt) {
+  const double h = 0.5 * dt;
+  return StepAbc{{h * p.A, h * p.B, h * p.C}, {dt * p.A, dt * p.B, dt * p.C}};
+}
+
 // Largest displacement per coordinate for which a step's midpoint and end
 // point sines come from its start point by angle addition without a check.
 constexpr double kShiftLimit = 1.0 / 64;
@@ -225,8 +237,8 @@ struct CkptArgs {
   int64_t n;
   int64_t nsteps;
   int64_t k;
-  double dt;
-  AbcParams abc;
+  StepAbc step;
+  int32_t tier;  // shift_tier of dt and the amplitudes
 };
 hipError_t launch_rk2_forward_ckpt(const CkptArgs& a, hipStream_t s);
 
@@ -245,7 +257,8 @@ struct AdjointArgs {
   int64_t nsteps;
   int64_t k;
   double dt;
-  AbcParams abc;
+  StepAbc step;
+  int32_t tier;  // shift_tier of dt and the amplitudes
 };
 // number of per-block partial sums launch_adjoint needs (3 doubles each)
 int64_t adjoint_partials(int64_t n);
