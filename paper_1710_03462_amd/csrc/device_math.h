@@ -19,12 +19,6 @@ namespace soax {
 // Periodic box edge: the double nearest to 2*pi.
 constexpr double kBoxL = 6.283185307179586;
 
-struct Abc {
-  double A, B, C;
-};
-
-__device__ __forceinline__ Abc to_abc(const AbcParams& p) { return Abc{p.A, p.B, p.C}; }
-
 // Wrap one coordinate displaced by much less than a box edge into [0, L).
 // A negative coordinate whose sum with L rounds to L is stored as 0.
 __device__ __forceinline__ double wrap_box(double x) {
@@ -93,7 +87,7 @@ __device__ __forceinline__ Trig3 trig3_shift(const Trig3& t, double x, double y,
   return r;
 }
 
-static_assert(kShiftLimit == trig::kShiftMax, "small_steps must match the shift bound");
+static_assert(kShiftLimit == trig::kShiftMax, "the small tier must match the shift bound");
 static_assert(kShiftMidLimit < trig::kShiftLong, "the mid tier must stay inside the long series");
 static_assert(kTierSmall == trig::kTierSmall && kTierMid == trig::kTierMid &&
                   kTierAny == trig::kTierAny,
@@ -101,37 +95,28 @@ static_assert(kTierSmall == trig::kTierSmall && kTierMid == trig::kTierMid &&
 
 // u = (A sin z + C cos y, B sin x + A cos z, C sin y + B cos x), each
 // component one product and one fused multiply-add
-__device__ __forceinline__ void field_of(const Abc& p, const Trig3& t, double& u0, double& u1,
+__device__ __forceinline__ void field_of(const AbcParams& p, const Trig3& t, double& u0, double& u1,
                                          double& u2) {
   u0 = fma(p.A, t.sz, p.C * t.cy);
   u1 = fma(p.B, t.sx, p.A * t.cz);
   u2 = fma(p.C, t.sy, p.B * t.cx);
 }
 
-__device__ __forceinline__ void abc_field(const Abc& p, double x, double y, double z, double& u0,
+__device__ __forceinline__ void abc_field(const AbcParams& p, double x, double y, double z, double& u0,
                                           double& u1, double& u2) {
   field_of(p, trig3(x, y, z), u0, u1, u2);
 }
 
 // One explicit-midpoint step: k1 = u(x), xm = x + (dt/2) k1, k2 = u(xm),
-// x+ = x + dt k2.  On return x holds x+ (not wrapped), t the sines and
-// cosines at the start point and d = dt k2 the displacement.
+// x+ = x + dt k2.  t: the sines and cosines at the start point; d = dt k2, the
+// displacement.
 template <int TIER>
-__device__ __forceinline__ void rk2_midpoint_parts(const Abc& p, double dt, double& x, double& y,
-                                                   double& z, Trig3& t, double& d0, double& d1,
-                                                   double& d2) {
+__device__ __forceinline__ void rk2_parts(const StepAbc& p, double x, double y, double z,
+                                          Trig3& t, double& d0, double& d1, double& d2) {
   t = trig3(x, y, z);
   double k0, k1, k2;
-  field_of(p, t, k0, k1, k2);
-  const double h = 0.5 * dt;
-  const Trig3 tm = trig3_shift<TIER>(t, x, y, z, h * k0, h * k1, h * k2);
-  field_of(p, tm, k0, k1, k2);
-  d0 = dt * k0;
-  d1 = dt * k1;
-  d2 = dt * k2;
-  x = x + d0;
-  y = y + d1;
-  z = z + d2;
+  field_of(p.h, t, k0, k1, k2);
+  field_of(p.d, trig3_shift<TIER>(t, x, y, z, k0, k1, k2), d0, d1, d2);
 }
 
 // Alignment (bytes) of a run of VEC consecutive T starting at a multiple of
@@ -334,57 +319,49 @@ __device__ __forceinline__ void euler_component(PT& x, VT& v, VT a, double dt, i
 // One Heun step (explicit trapezoid): k1 = u(x), k2 = u(x + dt k1),
 // d = (dt/2)(k1 + k2); t holds the start point's sines and cosines.
 template <int TIER>
-__device__ __forceinline__ void heun_parts(const Abc& p, double dt, double x, double y, double z,
+__device__ __forceinline__ void heun_parts(const StepAbc& p, double x, double y, double z,
                                            Trig3& t, double& d0, double& d1, double& d2) {
   t = trig3(x, y, z);
   double a0, a1, a2, b0, b1, b2;
-  field_of(p, t, a0, a1, a2);
-  field_of(p, trig3_shift<TIER>(t, x, y, z, dt * a0, dt * a1, dt * a2), b0, b1, b2);
-  const double h = 0.5 * dt;
-  d0 = h * (a0 + b0);
-  d1 = h * (a1 + b1);
-  d2 = h * (a2 + b2);
+  field_of(p.d, t, a0, a1, a2);
+  field_of(p.d, trig3_shift<TIER>(t, x, y, z, a0, a1, a2), b0, b1, b2);
+  d0 = 0.5 * (a0 + b0);
+  d1 = 0.5 * (a1 + b1);
+  d2 = 0.5 * (a2 + b2);
 }
 
 // One classical RK4 step: k1 = u(x), k2 = u(x + dt/2 k1), k3 = u(x + dt/2 k2),
-// k4 = u(x + dt k3), d = dt/6 (k1 + 2 k2 + 2 k3 + k4); every stage's sines come
-// from the start point's by angle addition.
+// k4 = u(x + dt k3), d = dt/6 (k1 + 2 k2 + 2 k3 + k4), here as
+// (a + 2 b + c + e)/3 with a, b, e = dt/2 (k1, k2, k4) and c = dt k3; every
+// stage's sines come from the start point's by rotation.
 template <int TIER>
-__device__ __forceinline__ void rk4_parts(const Abc& p, double dt, double x, double y, double z,
+__device__ __forceinline__ void rk4_parts(const StepAbc& p, double x, double y, double z,
                                           Trig3& t, double& d0, double& d1, double& d2) {
   t = trig3_joined(x, y, z);
-  const double h = 0.5 * dt;
-  double k10, k11, k12, k20, k21, k22, k30, k31, k32, k40, k41, k42;
-  field_of(p, t, k10, k11, k12);
-  field_of(p, trig3_shift<TIER>(t, x, y, z, h * k10, h * k11, h * k12), k20, k21, k22);
-  field_of(p, trig3_shift<TIER>(t, x, y, z, h * k20, h * k21, h * k22), k30, k31, k32);
-  field_of(p, trig3_shift<TIER>(t, x, y, z, dt * k30, dt * k31, dt * k32), k40, k41, k42);
-  const double s = dt / 6.0;
-  d0 = s * (k10 + 2.0 * k20 + 2.0 * k30 + k40);
-  d1 = s * (k11 + 2.0 * k21 + 2.0 * k31 + k41);
-  d2 = s * (k12 + 2.0 * k22 + 2.0 * k32 + k42);
+  double a0, a1, a2, b0, b1, b2, c0, c1, c2, e0, e1, e2;
+  field_of(p.h, t, a0, a1, a2);
+  field_of(p.h, trig3_shift<TIER>(t, x, y, z, a0, a1, a2), b0, b1, b2);
+  field_of(p.d, trig3_shift<TIER>(t, x, y, z, b0, b1, b2), c0, c1, c2);
+  field_of(p.h, trig3_shift<TIER>(t, x, y, z, c0, c1, c2), e0, e1, e2);
+  constexpr double kThird = 1.0 / 3.0;
+  d0 = kThird * ((fma(2.0, b0, a0) + c0) + e0);
+  d1 = kThird * ((fma(2.0, b1, a1) + c1) + e1);
+  d2 = kThird * ((fma(2.0, b2, a2) + c2) + e2);
 }
 
 // The positions (y0, y1, y2) one step of a field integrator after
 // (s0, s1, s2), not wrapped; t: the start point's sines and cosines, d: the
-// displacement, from which the field at the new position follows by angle
-// addition.
+// displacement, from which the field at the new position follows by rotation.
 template <int INTEG, int TIER>
-__device__ __forceinline__ void field_step(const Abc& p, double dt, double s0, double s1,
-                                           double s2, double& y0, double& y1, double& y2,
-                                           Trig3& t, double& d0, double& d1, double& d2) {
-  if constexpr (INTEG == kRk2Abc) {
-    y0 = s0;
-    y1 = s1;
-    y2 = s2;
-    rk2_midpoint_parts<TIER>(p, dt, y0, y1, y2, t, d0, d1, d2);
-  } else {
-    if constexpr (INTEG == kHeunAbc) heun_parts<TIER>(p, dt, s0, s1, s2, t, d0, d1, d2);
-    else rk4_parts<TIER>(p, dt, s0, s1, s2, t, d0, d1, d2);
-    y0 = s0 + d0;
-    y1 = s1 + d1;
-    y2 = s2 + d2;
-  }
+__device__ __forceinline__ void field_step(const StepAbc& p, double s0, double s1, double s2,
+                                           double& y0, double& y1, double& y2, Trig3& t,
+                                           double& d0, double& d1, double& d2) {
+  if constexpr (INTEG == kRk2Abc) rk2_parts<TIER>(p, s0, s1, s2, t, d0, d1, d2);
+  else if constexpr (INTEG == kHeunAbc) heun_parts<TIER>(p, s0, s1, s2, t, d0, d1, d2);
+  else rk4_parts<TIER>(p, s0, s1, s2, t, d0, d1, d2);
+  y0 = s0 + d0;
+  y1 = s1 + d1;
+  y2 = s2 + d2;
 }
 
 // Advance one particle.  Positions and velocities are widened to double,
@@ -392,7 +369,7 @@ __device__ __forceinline__ void field_step(const Abc& p, double dt, double s0, d
 // step (field integrators only; the results do not depend on it).
 template <int INTEG, typename PT, typename VT, int TIER>
 __device__ __forceinline__ void update_particle(PT& x0, PT& x1, PT& x2, VT& v0, VT& v1, VT& v2,
-                                                VT a0, VT a1, VT a2, double dt, const Abc& p,
+                                                VT a0, VT a1, VT a2, double dt, const StepAbc& p,
                                                 int wrap) {
   if constexpr (INTEG == kSymEuler) {
     euler_component<INTEG, PT, VT>(x0, v0, a0, dt, wrap);
@@ -418,7 +395,7 @@ __device__ __forceinline__ void update_particle(PT& x0, PT& x1, PT& x2, VT& v0, 
     double y0, y1, y2;
     Trig3 t;
     double d0, d1, d2;
-    field_step<INTEG, TIER>(p, dt, s0, s1, s2, y0, y1, y2, t, d0, d1, d2);
+    field_step<INTEG, TIER>(p, s0, s1, s2, y0, y1, y2, t, d0, d1, d2);
     if (wrap) wrap_box3(y0, y1, y2);
     x0 = static_cast<PT>(y0);
     x1 = static_cast<PT>(y1);
@@ -426,7 +403,7 @@ __device__ __forceinline__ void update_particle(PT& x0, PT& x1, PT& x2, VT& v0, 
     // the stored velocity is the field at the new position (the field is
     // 2pi-periodic, so the shift from the start point needs no wrap)
     double u0, u1, u2;
-    field_of(p, trig3_shift<TIER>(t, s0, s1, s2, d0, d1, d2), u0, u1, u2);
+    field_of(p.u, trig3_shift<TIER>(t, s0, s1, s2, d0, d1, d2), u0, u1, u2);
     v0 = static_cast<VT>(u0);
     v1 = static_cast<VT>(u1);
     v2 = static_cast<VT>(u2);

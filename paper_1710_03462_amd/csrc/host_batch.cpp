@@ -121,10 +121,7 @@ soax_status upload_params(soax_batch* b, const double* dt, const double* abc, hi
   for (size_t i = 0; i < b->sets.size(); ++i) {
     b->stage[i].tier = shift_tier(dt[i], abc[3 * i], abc[3 * i + 1], abc[3 * i + 2]);
     b->max_tier = std::max(b->max_tier, static_cast<int>(b->stage[i].tier));
-    b->stage[i].dt = dt[i];
-    b->stage[i].A = abc[3 * i];
-    b->stage[i].B = abc[3 * i + 1];
-    b->stage[i].C = abc[3 * i + 2];
+    b->stage[i].abc = step_abc(AbcParams{abc[3 * i], abc[3 * i + 1], abc[3 * i + 2]}, dt[i]);
   }
   HIP_TRY(hipMemcpyAsync(b->dev_sets, b->stage, b->sets.size() * sizeof(BatchSet),
                          hipMemcpyHostToDevice, s),
@@ -156,7 +153,7 @@ soax_status per_set_step(soax_batch* b, const double* dt, const double* abc, hip
     }
     a.n = set->n;
     a.dt = dt[i];
-    a.abc = AbcParams{abc[3 * i], abc[3 * i + 1], abc[3 * i + 2]};
+    a.abc = step_abc(AbcParams{abc[3 * i], abc[3 * i + 1], abc[3 * i + 2]}, dt[i]);
     a.wrap = 1;
     // one particle per thread, 128 threads: the faster shape for this mode's
     // mostly cache-resident sets (two per thread in 64 threads took 174 ms

@@ -54,9 +54,9 @@ template <int TIER, bool RENEW>
 __device__ __forceinline__ void rk2_advance_to(const StepAbc& p, double& x, double& y, double& z,
                                                Trig3& t) {
   double m0, m1, m2;
-  field_of(to_abc(p.h), t, m0, m1, m2);
+  field_of(p.h, t, m0, m1, m2);
   const Trig3 tm = trig3_shift<TIER>(t, x, y, z, m0, m1, m2);
-  field_of(to_abc(p.d), tm, m0, m1, m2);
+  field_of(p.d, tm, m0, m1, m2);
   const double x1 = x + m0, y1 = y + m1, z1 = z + m2;
   if (RENEW || TIER == kTierAny)
     t = trig3(x1, y1, z1);
@@ -182,7 +182,7 @@ __device__ __forceinline__ void rk2_reverse(const StepAbc& p, const Trig3& t, do
                                             double z, double& l0, double& l1, double& l2,
                                             double& g0, double& g1, double& g2) {
   double h0, h1, h2;  // (dt/2) u(x), as in the forward step
-  field_of(to_abc(p.h), t, h0, h1, h2);
+  field_of(p.h, t, h0, h1, h2);
   const Trig3 m = trig3_shift<TIER>(t, x, y, z, h0, h1, h2);  // at xm
   const double r0 = fma(m.cx, l1, -(m.sx * l2));
   const double r1 = fma(m.cy, l2, -(m.sy * l0));

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(1024) void soa_step_kernel(SoaStepArgs a) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t i0 = t * VEC;
   if (i0 >= a.n) return;
-  const Abc p = to_abc(a.abc);
+  const StepAbc& p = a.abc;
   PT* px = static_cast<PT*>(a.pos[0]);
   PT* py = static_cast<PT*>(a.pos[1]);
   PT* pz = static_cast<PT*>(a.pos[2]);
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(1024) void soa_step_kernel(SoaStepArgs a) {
 // shape.
 template <typename PT, typename VT, int VEC, int TIER>
 __global__ __launch_bounds__(1024) void soa_rk4_two_runs_kernel(SoaStepArgs a) {
-  const Abc p = to_abc(a.abc);
+  const StepAbc& p = a.abc;
   PT* px = static_cast<PT*>(a.pos[0]);
   PT* py = static_cast<PT*>(a.pos[1]);
   PT* pz = static_cast<PT*>(a.pos[2]);
@@ -286,7 +286,7 @@ hipError_t soa_step_vec(int vec, int block, const SoaStepArgs& a, hipStream_t s)
   const int64_t bytes = soa_step_bytes(INTEG, sizeof(PT), sizeof(VT));
   const bool stream = a.n * bytes >= kStreamBytes;
   if constexpr (field_integrator(INTEG)) {
-    const int tier = shift_tier(a.dt, a.abc.A, a.abc.B, a.abc.C);
+    const int tier = shift_tier(a.dt, a.abc.u.A, a.abc.u.B, a.abc.u.C);
     if (tier == kTierSmall)
       return soa_step_stream<INTEG, PT, VT, kTierSmall>(stream, vec, grid, block, a, s);
     if (tier == kTierMid)
@@ -307,7 +307,7 @@ template <int INTEG, typename PT, typename VT, int TIER>
 __global__ __launch_bounds__(256) void soa_fused_kernel(SoaStepArgs a, int64_t nsteps) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  const Abc p = to_abc(a.abc);
+  const StepAbc& p = a.abc;
   PT* px = static_cast<PT*>(a.pos[0]);
   PT* py = static_cast<PT*>(a.pos[1]);
   PT* pz = static_cast<PT*>(a.pos[2]);
@@ -323,14 +323,14 @@ __global__ __launch_bounds__(256) void soa_fused_kernel(SoaStepArgs a, int64_t n
       s1 = y;
       s2 = z;
       double y0, y1, y2;
-      field_step<INTEG, TIER>(p, a.dt, s0, s1, s2, y0, y1, y2, t, d0, d1, d2);
+      field_step<INTEG, TIER>(p, s0, s1, s2, y0, y1, y2, t, d0, d1, d2);
       if (a.wrap) wrap_box3(y0, y1, y2);
       x = y0;
       y = y1;
       z = y2;
     }
     double u0, u1, u2;
-    field_of(p, trig3_shift<TIER>(t, s0, s1, s2, d0, d1, d2), u0, u1, u2);
+    field_of(p.u, trig3_shift<TIER>(t, s0, s1, s2, d0, d1, d2), u0, u1, u2);
     vx[i] = static_cast<VT>(u0);
     vy[i] = static_cast<VT>(u1);
     vz[i] = static_cast<VT>(u2);
@@ -360,7 +360,7 @@ hipError_t soa_fused_launch(int block, const SoaStepArgs& a, int64_t nsteps, hip
   const int64_t grid = (a.n + block - 1) / block;
   if (grid == 0 || nsteps <= 0) return hipSuccess;
   int tier = kTierAny;
-  if constexpr (field_integrator(INTEG)) tier = shift_tier(a.dt, a.abc.A, a.abc.B, a.abc.C);
+  if constexpr (field_integrator(INTEG)) tier = shift_tier(a.dt, a.abc.u.A, a.abc.u.B, a.abc.u.C);
   if (tier == kTierSmall)
     hipLaunchKernelGGL((soa_fused_kernel<INTEG, PT, VT, kTierSmall>), dim3(grid), dim3(block), 0,
                        s, a, nsteps);
@@ -397,7 +397,7 @@ __device__ __forceinline__ void rec_store(char* p, T v) {
 
 // Update the record at `rec` (in LDS or global memory) in place.
 template <int INTEG, typename PT, typename VT, bool ALIGNED, int TIER>
-__device__ __forceinline__ void update_record(char* rec, const AosStepArgs& a, const Abc& p) {
+__device__ __forceinline__ void update_record(char* rec, const AosStepArgs& a, const StepAbc& p) {
   char* P = rec + a.off_pos;
   char* V = rec + a.off_vel;
   PT x = rec_load<PT, ALIGNED>(P), y = rec_load<PT, ALIGNED>(P + sizeof(PT)),
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(1024) void aos_step_kernel(AosStepArgs a, int tile)
   const int nbytes = nrec * a.stride;
   stage_in<STREAM>(lds, g, nbytes);
   __syncthreads();
-  const Abc p = to_abc(a.abc);
+  const StepAbc& p = a.abc;
   for (int r = threadIdx.x; r < nrec; r += blockDim.x)
     update_record<INTEG, PT, VT, ALIGNED, TIER>(lds + r * a.stride, a, p);
   __syncthreads();
@@ -491,7 +491,7 @@ template <int INTEG, typename PT, typename VT, bool ALIGNED, int TIER>
 __global__ __launch_bounds__(1024) void aos_naive_kernel(AosStepArgs a) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  update_record<INTEG, PT, VT, ALIGNED, TIER>(a.aos + i * a.stride, a, to_abc(a.abc));
+  update_record<INTEG, PT, VT, ALIGNED, TIER>(a.aos + i * a.stride, a, a.abc);
 }
 
 template <int INTEG, typename PT, typename VT, int TIER>
@@ -530,7 +530,7 @@ template <int INTEG, typename PT, typename VT>
 hipError_t aos_step_t(bool aligned, bool naive, int block, const AosStepArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   if constexpr (field_integrator(INTEG)) {
-    const int tier = shift_tier(a.dt, a.abc.A, a.abc.B, a.abc.C);
+    const int tier = shift_tier(a.dt, a.abc.u.A, a.abc.u.B, a.abc.u.C);
     if (tier == kTierSmall)
       return aos_step_launch<INTEG, PT, VT, kTierSmall>(aligned, naive, block, a, s);
     if (tier == kTierMid)
@@ -755,7 +755,7 @@ template <int INTEG, typename PT, typename VT, int TIER, bool STREAM>
 __global__ __launch_bounds__(1024) void aosoa_step_kernel(AosoaStepArgs a) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
-  const Abc p = to_abc(a.abc);
+  const StepAbc& p = a.abc;
   // a workgroup is whole waves (the host launches multiples of 64 threads)
   // and a tile is 64 particles, so every lane of a wave is in the same tile
   const int64_t tile = __builtin_amdgcn_readfirstlane(static_cast<int>(i / kAosoaW));
@@ -807,7 +807,7 @@ hipError_t aosoa_step_t(int block, const AosoaStepArgs& a, hipStream_t s) {
   if (uses_acc(INTEG)) bytes += 3 * sizeof(VT);
   const bool stream = a.n * bytes >= kStreamBytes;
   int tier = kTierAny;
-  if constexpr (field_integrator(INTEG)) tier = shift_tier(a.dt, a.abc.A, a.abc.B, a.abc.C);
+  if constexpr (field_integrator(INTEG)) tier = shift_tier(a.dt, a.abc.u.A, a.abc.u.B, a.abc.u.C);
 #define SOAX_AOSOA(TI, ST) \
   hipLaunchKernelGGL((aosoa_step_kernel<INTEG, PT, VT, TI, ST>), dim3(grid), dim3(block), 0, s, a)
   if (tier == kTierSmall && stream) SOAX_AOSOA(kTierSmall, true);
@@ -895,7 +895,7 @@ __global__ __launch_bounds__(256) void vel_from_field_kernel(SoaStepArgs a) {
   const PT* py = static_cast<const PT*>(a.pos[1]);
   const PT* pz = static_cast<const PT*>(a.pos[2]);
   double u0, u1, u2;
-  abc_field(to_abc(a.abc), widen(px[i]), widen(py[i]), widen(pz[i]), u0, u1, u2);
+  abc_field(a.abc.u, widen(px[i]), widen(py[i]), widen(pz[i]), u0, u1, u2);
   static_cast<VT*>(a.vel[0])[i] = static_cast<VT>(u0);
   static_cast<VT*>(a.vel[1])[i] = static_cast<VT>(u1);
   static_cast<VT*>(a.vel[2])[i] = static_cast<VT>(u2);

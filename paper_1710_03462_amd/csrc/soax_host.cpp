@@ -161,7 +161,7 @@ soax_status soax_fill(soax_set* set, uint64_t seed, int32_t vel_mode, const soax
       a.vel[d] = set->soa[L.f[fvel].first_array + d];
     }
     a.n = set->n;
-    a.abc = AbcParams{params->A, params->B, params->C};
+    a.abc.u = AbcParams{params->A, params->B, params->C};
     HIP_TRY(launch_vel_from_field(L.f[fpos].dtype, L.f[fvel].dtype, a, s), "field fill launch");
   }
   return SOAX_OK;
@@ -200,7 +200,7 @@ soax_status soax_step(soax_set* set, int32_t layout, int32_t integrator, double 
   }
   const int wrap = params ? params->wrap : 0;
   if (wrap != 0 && wrap != 1) return fail(SOAX_E_ARG, "params.wrap must be 0 or 1");
-  AbcParams abc{0.0, 0.0, 0.0};
+  StepAbc abc{};
   if (field_integrator(integrator)) {
     if (!params) return fail(SOAX_E_ARG, "integrating in the ABC field needs params");
     if (L.f[fp].dtype != kF64) return fail(SOAX_E_SCHEMA, "integrating in the ABC field needs f64 'pos'");
@@ -208,7 +208,7 @@ soax_status soax_step(soax_set* set, int32_t layout, int32_t integrator, double 
   if (params) {
     if (!is_finite(params->A) || !is_finite(params->B) || !is_finite(params->C))
       return fail(SOAX_E_ARG, "field amplitudes must be finite");
-    abc = AbcParams{params->A, params->B, params->C};
+    abc = step_abc(AbcParams{params->A, params->B, params->C}, dt);
   }
   if (wrap && L.f[fp].dtype != kF64) return fail(SOAX_E_SCHEMA, "the periodic wrap needs f64 'pos'");
   hipStream_t s = as_stream(stream);
@@ -328,7 +328,7 @@ soax_status soax_step_fused(soax_set* set, int32_t integrator, double dt, int64_
   }
   a.n = set->n;
   a.dt = dt;
-  if (params) a.abc = AbcParams{params->A, params->B, params->C};
+  if (params) a.abc = step_abc(AbcParams{params->A, params->B, params->C}, dt);
   a.wrap = params ? params->wrap : 0;
   // one particle per thread: the loop over steps is bound by arithmetic, and
   // the arrays are touched once per call
