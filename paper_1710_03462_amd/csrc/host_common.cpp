@@ -178,9 +178,9 @@ soax_status alloc_owned(const Layout& L, int64_t cap, void** soa_block, std::vec
 void free_set(soax_set* s) {
   if (!s) return;
   if (s->aosoa_dev) (void)hipFree(s->aosoa_dev);
-  if (s->pinned_pending) (void)hipEventSynchronize(s->pinned_done);
-  if (s->pinned_done) (void)hipEventDestroy(s->pinned_done);
-  if (s->pinned) (void)hipHostFree(s->pinned);
+  if (s->pinned_count) (void)hipHostFree(s->pinned_count);
+  for (void* p : s->scratch)
+    if (p) (void)hipFree(p);
   if (s->xpose_dev) (void)hipFree(s->xpose_dev);
   if (s->owned_soa) (void)hipFree(s->owned_soa);
   if (s->owned_aos) (void)hipFree(s->owned_aos);

@@ -74,25 +74,6 @@ soax_status set_size(soax_set* set, int64_t n) {
   return SOAX_OK;
 }
 
-// Pinned host scratch of at least `bytes`, once its last use has finished.
-soax_status pinned_scratch(soax_set* set, size_t bytes, void** p) {
-  if (set->pinned_pending) {
-    HIP_TRY(hipEventSynchronize(set->pinned_done), "hipEventSynchronize");
-    set->pinned_pending = false;
-  }
-  if (!set->pinned_done)
-    HIP_TRY(hipEventCreateWithFlags(&set->pinned_done, hipEventDisableTiming), "hipEventCreate");
-  if (set->pinned_bytes < bytes) {
-    if (set->pinned) (void)hipHostFree(set->pinned);
-    set->pinned = nullptr;
-    set->pinned_bytes = 0;
-    HIP_TRY(hipHostMalloc(&set->pinned, bytes, hipHostMallocDefault), "hipHostMalloc");
-    set->pinned_bytes = bytes;
-  }
-  *p = set->pinned;
-  return SOAX_OK;
-}
-
 // Width in bytes of the moves of one AoS record: the widest of 16, 8, 4
 // that divides the stride and the buffer's alignment.
 int record_word(const soax_set* set) {
@@ -113,6 +94,29 @@ struct DevBuf {  // stream-ordered scratch, released on the same stream
     if (p) (void)hipFreeAsync(p, s);
   }
 };
+
+// Scratch `which` of the set, at least `bytes`: the buffer the set keeps
+// (allocating and releasing it on each call costs about 10 us of host time),
+// or, beyond kKeptScratch, `own`, released when the call ends.
+hipError_t set_scratch(soax_set* set, int which, size_t bytes, hipStream_t s, DevBuf& own,
+                       void** p) {
+  if (bytes > kKeptScratch) {
+    const hipError_t e = own.alloc(bytes, s);
+    *p = own.p;
+    return e;
+  }
+  if (set->scratch_bytes[which] < bytes) {
+    if (set->scratch[which]) (void)hipFreeAsync(set->scratch[which], s);
+    set->scratch[which] = nullptr;
+    set->scratch_bytes[which] = 0;
+    const size_t size = std::min(kKeptScratch, 2 * bytes);
+    const hipError_t e = hipMallocAsync(&set->scratch[which], size, s);
+    if (e != hipSuccess) return e;
+    set->scratch_bytes[which] = size;
+  }
+  *p = set->scratch[which];
+  return hipSuccess;
+}
 
 }  // namespace
 
@@ -145,15 +149,16 @@ soax_status soax_resize(soax_set* set, int64_t n, void* stream) {
   if ((st = ensure_capacity(set, n, s))) return st;
   if (n > set->n) {
     const int64_t add = n - set->n;
+    ZeroArgs z{};
+    auto part = [&](void* p, int64_t size) {
+      z.base[z.parts] = static_cast<char*>(p) + set->n * size;
+      z.bytes[z.parts++] = add * size;
+    };
     if (has_soa(set))
       for (const Field& f : set->L.f)
-        for (int c = 0; c < f.dim; ++c)
-          HIP_TRY(launch_zero(static_cast<char*>(set->soa[f.first_array + c]) + set->n * f.es,
-                              add * f.es, s),
-                  "zero fill launch");
-    if (set->aos)
-      HIP_TRY(launch_zero(set->aos + set->n * set->L.stride, add * set->L.stride, s),
-              "zero fill launch");
+        for (int c = 0; c < f.dim; ++c) part(set->soa[f.first_array + c], f.es);
+    if (set->aos) part(set->aos, set->L.stride);
+    HIP_TRY(launch_zero(z, s), "zero fill launch");
   }
   return set_size(set, n);
 }
@@ -271,64 +276,45 @@ soax_status soax_remove_flagged(soax_set* set, const uint8_t* flags, int64_t* ne
   if (n == 0) return SOAX_OK;
   const hipStream_t s = as_stream(stream);
   const int64_t tiles = container_tiles(n);
-  // pinned staging: tile counts (int32), then the two offset tables (int64)
-  const size_t counts_bytes = (tiles * sizeof(int32_t) + 15) & ~size_t(15);
-  void* host = nullptr;
-  soax_status st;
-  if ((st = pinned_scratch(set, counts_bytes + 2 * tiles * sizeof(int64_t), &host))) return st;
-  int32_t* counts = static_cast<int32_t*>(host);
-  int64_t* tab = reinterpret_cast<int64_t*>(static_cast<char*>(host) + counts_bytes);
-  DevBuf dcounts;
-  HIP_TRY(dcounts.alloc(tiles * sizeof(int32_t), s), "hipMallocAsync(counts)");
-  int32_t* dc = static_cast<int32_t*>(dcounts.p);
-  HIP_TRY(launch_count_flags(flags, n, dc, s), "flag count launch");
-  HIP_TRY(hipMemcpyAsync(counts, dc, tiles * sizeof(int32_t), hipMemcpyDeviceToHost, s),
-          "hipMemcpyAsync(counts)");
+  if (!set->pinned_count)
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&set->pinned_count), sizeof(int32_t),
+                          hipHostMallocDefault),
+            "hipHostMalloc");
+  DevBuf own_table, own_lists;
+  void* table = nullptr;  // tile counts and their exclusive sums
+  HIP_TRY(set_scratch(set, 0, 2 * tiles * sizeof(int32_t), s, own_table, &table),
+          "hipMallocAsync(counts)");
+  int32_t* counts = static_cast<int32_t*>(table);
+  int32_t* before = counts + tiles;
+  HIP_TRY(launch_count_flags(flags, n, counts, before, set->pinned_count, s),
+          "flag count launch");
   HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");  // the one wait: n' is returned
-  int64_t m = 0;
-  for (int64_t b = 0; b < tiles; ++b) m += counts[b];
+  const int64_t m = *set->pinned_count;
   const int64_t n_new = n - m;
   const int64_t moves_max = std::min(m, n_new);
   if (moves_max > 0) {
-    // tab[b]: flagged in tiles < b; tab[tiles + b]: unflagged in tiles > b
-    const int64_t T = container_tile_size();
-    int64_t acc = 0;
-    for (int64_t b = 0; b < tiles; ++b) {
-      tab[b] = acc;
-      acc += counts[b];
-    }
-    acc = 0;
-    for (int64_t b = tiles - 1; b >= 0; --b) {
-      tab[tiles + b] = acc;
-      acc += std::min(T, n - b * T) - counts[b];
-    }
     MoveArgs mv{};
-    if (has_soa(set))
-      for (const Field& f : set->L.f)
-        for (int c = 0; c < f.dim; ++c) {
-          mv.base[mv.narrays] = static_cast<char*>(set->soa[f.first_array + c]);
-          mv.stride[mv.narrays] = f.es;
-          mv.word[mv.narrays] = f.es;
-          ++mv.narrays;
-        }
-    if (set->aos) {
-      mv.base[mv.narrays] = set->aos;
-      mv.stride[mv.narrays] = static_cast<int32_t>(set->L.stride);
-      mv.word[mv.narrays] = record_word(set);
-      ++mv.narrays;
+    int y = 0;
+    const int sizes[3] = {8, 4, 1};
+    for (int g = 0; g < 3; ++g) {
+      if (has_soa(set))
+        for (const Field& f : set->L.f)
+          for (int c = 0; c < f.dim && f.es == sizes[g]; ++c)
+            mv.base[y++] = static_cast<char*>(set->soa[f.first_array + c]);
+      mv.group_end[g] = y;
     }
-    DevBuf dtab, dlists;
-    HIP_TRY(dtab.alloc(2 * tiles * sizeof(int64_t), s), "hipMallocAsync(offsets)");
-    HIP_TRY(dlists.alloc((2 * moves_max + 1) * sizeof(int64_t), s), "hipMallocAsync(lists)");
-    int64_t* dt = static_cast<int64_t*>(dtab.p);
-    int64_t* hole_at = static_cast<int64_t*>(dlists.p);
-    int64_t* mover_at = hole_at + moves_max;
-    int64_t* nmoves = mover_at + moves_max;
-    HIP_TRY(hipMemcpyAsync(dt, tab, 2 * tiles * sizeof(int64_t), hipMemcpyHostToDevice, s),
-            "hipMemcpyAsync(offsets)");
-    HIP_TRY(hipEventRecord(set->pinned_done, s), "hipEventRecord");
-    set->pinned_pending = true;
-    HIP_TRY(launch_rank_flags(flags, n, n_new, dt, dt + tiles, hole_at, mover_at, nmoves, s),
+    if (set->aos) {
+      mv.record = set->aos;
+      mv.record_stride = static_cast<int32_t>(set->L.stride);
+      mv.record_word = record_word(set);
+    }
+    void* lists = nullptr;
+    HIP_TRY(set_scratch(set, 1, (2 * moves_max + 1) * sizeof(int32_t), s, own_lists, &lists),
+            "hipMallocAsync(lists)");
+    int32_t* hole_at = static_cast<int32_t*>(lists);
+    int32_t* mover_at = hole_at + moves_max;
+    int32_t* nmoves = mover_at + moves_max;
+    HIP_TRY(launch_rank_flags(flags, n, n_new, before, hole_at, mover_at, nmoves, s),
             "rank launch");
     HIP_TRY(launch_move_all(mv, hole_at, mover_at, nmoves, moves_max, s), "move launch");
   }

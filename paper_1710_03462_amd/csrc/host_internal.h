@@ -27,6 +27,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
 constexpr int64_t kMaxParticles = INT32_MAX;
+constexpr size_t kKeptScratch = size_t(32) << 20;
 
 struct Field {
   std::string name;
@@ -89,12 +90,13 @@ struct soax_set {
   int64_t aosoa_bytes = 0;
   soax::XposeArgs* aosoa_dev = nullptr;
   soax::XposeArgs aosoa_host{};
-  // pinned host staging of the removal's tile counts and offsets, reused
-  // once the event says the last copy out of it has finished
-  void* pinned = nullptr;
-  size_t pinned_bytes = 0;
-  hipEvent_t pinned_done = nullptr;
-  bool pinned_pending = false;
+  // pinned host word for the removal's flag count (read before the call
+  // that asked for it returns)
+  int32_t* pinned_count = nullptr;
+  // device scratch of the removal, kept for the set's next one up to
+  // kKeptScratch bytes each: the tile sums, and the lists of moves
+  void* scratch[2] = {nullptr, nullptr};
+  size_t scratch_bytes[2] = {0, 0};
 };
 
 namespace soax {

@@ -271,35 +271,41 @@ hipError_t launch_sqdist_loss(const LossArgs& a, hipStream_t s);
 
 // ------------------------------------------------------------- containers
 
-// Removal with overwrite-by-last in three passes over a flag array (one
-// byte per particle, nonzero = remove) split into tiles of
-// container_tile_size() particles.
-int64_t container_tile_size();
+// Removal with overwrite-by-last in four passes over a flag array (one byte
+// per particle, nonzero = remove) split into tiles.  Particle numbers and
+// counts are below 2^31.
 int64_t container_tiles(int64_t n);
-// counts[b] = flagged particles in tile b.
-hipError_t launch_count_flags(const uint8_t* flags, int64_t n, int32_t* counts, hipStream_t s);
-// With holes_before[b] = flagged particles in tiles before b and
-// movers_after[b] = unflagged particles in tiles after b: hole_at[k] = k-th
-// flagged slot below n_new (ascending), mover_at[k] = k-th unflagged particle
-// at or above n_new counted from the end, and *nmoves = flagged slots below
-// n_new.  Both lists need min(n - n_new, n_new) entries.
-hipError_t launch_rank_flags(const uint8_t* flags, int64_t n, int64_t n_new,
-                             const int64_t* holes_before, const int64_t* movers_after,
-                             int64_t* hole_at, int64_t* mover_at, int64_t* nmoves, hipStream_t s);
-// Every array of a set moved by one launch: for k < *nmoves and every listed
-// array, element hole_at[k] <- element mover_at[k], `stride` bytes moved
-// `word` bytes at a time (word in {1, 4, 8, 16} divides stride and the
-// array's alignment).
+// counts[b] = flagged particles in tile b, before[b] = flagged particles in
+// tiles before b, and *total (pinned host memory) = flagged particles.
+hipError_t launch_count_flags(const uint8_t* flags, int64_t n, int32_t* counts, int32_t* before,
+                              int32_t* total, hipStream_t s);
+// hole_at[k] = k-th flagged slot below n_new (ascending), mover_at[k] = k-th
+// unflagged particle at or above n_new counted from the end, and *nmoves =
+// flagged slots below n_new (n_new >= 1).  Both lists need
+// min(n - n_new, n_new) entries.
+hipError_t launch_rank_flags(const uint8_t* flags, int64_t n, int64_t n_new, const int32_t* before,
+                             int32_t* hole_at, int32_t* mover_at, int32_t* nmoves, hipStream_t s);
+// Every array of a set moved by one launch: for k < *nmoves, element
+// hole_at[k] <- element mover_at[k] of every SoA array, listed by element
+// size (8, 4, then 1 byte; each aligned to it), and of the AoS records (null:
+// none), record_word bytes at a time (1, 4, 8 or 16, dividing the stride and
+// the buffer's alignment).
 struct MoveArgs {
-  int32_t narrays;
-  char* base[kMaxArrays + 1];
-  int32_t stride[kMaxArrays + 1];
-  int32_t word[kMaxArrays + 1];
+  char* base[kMaxArrays];
+  int32_t group_end[3];
+  char* record;
+  int32_t record_stride;
+  int32_t record_word;
 };
-hipError_t launch_move_all(const MoveArgs& m, const int64_t* hole_at, const int64_t* mover_at,
-                           const int64_t* nmoves, int64_t max_moves, hipStream_t s);
-// p[0, bytes) = 0.
-hipError_t launch_zero(void* p, int64_t bytes, hipStream_t s);
+hipError_t launch_move_all(const MoveArgs& m, const int32_t* hole_at, const int32_t* mover_at,
+                           const int32_t* nmoves, int64_t max_moves, hipStream_t s);
+// base[y][0, bytes[y]) = 0 for every part y.
+struct ZeroArgs {
+  char* base[kMaxArrays + 1];
+  int64_t bytes[kMaxArrays + 1];
+  int32_t parts;
+};
+hipError_t launch_zero(const ZeroArgs& z, hipStream_t s);
 
 // ------------------------------------------------------------ expressions
 
