@@ -115,7 +115,8 @@ struct AosStepArgs {
 };
 
 // LDS-staged tile kernel: needs a 16-byte aligned buffer; `aligned` says
-// every pos/vel/acc element is naturally aligned inside a record.
+// every pos/vel/acc element is naturally aligned inside a record; block 0
+// picks the shape.
 hipError_t launch_aos_step(int integ, int pos_t, int vel_t, bool aligned, int block,
                            const AosStepArgs& a, hipStream_t s);
 // One thread per record, direct per-field global accesses.

@@ -285,9 +285,9 @@ soax_status soax_step(soax_set* set, int32_t layout, int32_t integrator, double 
   if (reinterpret_cast<uintptr_t>(set->aos) % 8) aligned = false;
   if (layout == SOAX_AOS) {
     if (!set->aos_base_ok) return fail(SOAX_E_LAYOUT, "the AoS buffer is not 16-byte aligned");
-    const int block = set->block[SOAX_AOS] ? set->block[SOAX_AOS] : 256;
     for (int64_t k = 0; k < nsteps; ++k)
-      HIP_TRY(launch_aos_step(integrator, L.f[fp].dtype, L.f[fv].dtype, aligned, block, a, s),
+      HIP_TRY(launch_aos_step(integrator, L.f[fp].dtype, L.f[fv].dtype, aligned,
+                              set->block[SOAX_AOS], a, s),
               "AoS step launch");
   } else {
     const int block = set->block[SOAX_AOS_NAIVE] ? set->block[SOAX_AOS_NAIVE] : 256;
