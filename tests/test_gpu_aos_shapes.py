@@ -53,3 +53,23 @@ def test_small_records(stride_fields):
     ps.aos_to_soa()
     assert all(np.array_equal(g.cpu().numpy(), w.cpu().numpy()) for g, w in zip(ps.soa, want))
     ps.close()
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("extra", [0, 1, 2, 8, 9, 53, 54])  # 36 to 252 bytes
+def test_streaming_transpose_round_trip(extra, packed):
+    fields = [("id", "i32", 1), ("pos", "f64", 3), ("b", "u8", 1)]
+    fields += [(f"x{i}", "f32", 1) for i in range(min(extra, 24))]
+    fields += [(f"y{i}", "f64", 3) for i in range(max(0, extra - 49))]
+    stride = soax.Schema(fields, packed).layout()[1]
+    n = (128 << 20) // stride + 91
+    ps = soax.ParticleSet(fields, n, packed=packed)
+    ps.fill(seed=extra)
+    want = [t.clone() for t in ps.soa]
+    ps.soa_to_aos()
+    for t in ps.soa:
+        t.zero_()
+    ps.aos_to_soa()
+    for a, (g, w) in enumerate(zip(ps.soa, want)):
+        assert torch.equal(g.view(torch.uint8), w.view(torch.uint8)), (stride, a)
+    ps.close()
