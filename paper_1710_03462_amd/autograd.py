@@ -12,7 +12,7 @@ import ctypes
 import torch
 
 from ._lib import check, lib
-from .particles import current_stream
+from .particles import stream_handle
 
 
 # Rows of one checkpoint on the tape: the position and the sines and cosines
@@ -23,7 +23,8 @@ TAPE_ROWS = 9
 def _rows(t):
     """Row pointers of a contiguous [3, n] float64 tensor."""
     assert t.dtype == torch.float64 and t.is_contiguous() and t.shape[0] == 3
-    return (ctypes.c_void_p * 3)(*[t[d].data_ptr() for d in range(3)])
+    base, row = t.data_ptr(), 8 * t.stride(0)
+    return (ctypes.c_void_p * 3)(base, base + row, base + 2 * row)
 
 
 def _host3(abc):
@@ -38,7 +39,7 @@ def forward_ckpt(pos0, abc_host, dt, nsteps, k):
     nck = max(1, -(-int(nsteps) // int(k)))
     tape = torch.empty((nck, TAPE_ROWS, max(n, 1)), dtype=torch.float64, device=pos0.device)
     check(lib().soax_rk2_forward_ckpt(_rows(pos0), _rows(xT), n, abc_host, float(dt), int(nsteps),
-                                      int(k), ctypes.c_void_p(tape.data_ptr()), current_stream()),
+                                      int(k), ctypes.c_void_p(tape.data_ptr()), stream_handle()),
           "soax_rk2_forward_ckpt")
     return xT, tape
 
@@ -50,7 +51,7 @@ def adjoint(tape, lamT, abc_host, dt, nsteps, k):
     gabc = torch.empty(3, dtype=torch.float64, device=lamT.device)
     check(lib().soax_adjoint(ctypes.c_void_p(tape.data_ptr()), _rows(lamT), n, abc_host, float(dt),
                              int(nsteps), int(k), _rows(gx), ctypes.c_void_p(gabc.data_ptr()),
-                             current_stream()), "soax_adjoint")
+                             stream_handle()), "soax_adjoint")
     return gx, gabc
 
 
@@ -60,7 +61,7 @@ def sqdist_loss(xT, target, want_grad=True):
     loss = torch.empty(1, dtype=torch.float64, device=xT.device)
     lam = torch.empty_like(xT) if want_grad else None
     check(lib().soax_sqdist_loss(_rows(xT), _rows(target), n, _rows(lam) if want_grad else None,
-                                 ctypes.c_void_p(loss.data_ptr()), current_stream()),
+                                 ctypes.c_void_p(loss.data_ptr()), stream_handle()),
           "soax_sqdist_loss")
     return loss, lam
 
@@ -87,7 +88,7 @@ def forward_ckpt_records(x0_rec, xT_rec, pos_offset, stride, n, abc_host, dt, ns
                        device=x0_rec.device)
     check(lib().soax_rk2_forward_ckpt_strided(r0, rT, n, sd, abc_host, float(dt), int(nsteps),
                                               int(k), ctypes.c_void_p(tape.data_ptr()),
-                                              current_stream()), "soax_rk2_forward_ckpt_strided")
+                                              stream_handle()), "soax_rk2_forward_ckpt_strided")
     return tape
 
 
@@ -97,7 +98,7 @@ def sqdist_loss_records(xT_rec, target, lam_rec, pos_offset, stride, n):
     rl, _ = _record_rows(lam_rec, pos_offset, stride)
     loss = torch.empty(1, dtype=torch.float64, device=xT_rec.device)
     check(lib().soax_sqdist_loss_strided(rT, sd, _rows(target), n, rl,
-                                         ctypes.c_void_p(loss.data_ptr()), current_stream()),
+                                         ctypes.c_void_p(loss.data_ptr()), stream_handle()),
           "soax_sqdist_loss_strided")
     return loss
 
@@ -109,7 +110,7 @@ def adjoint_records(tape, lam_rec, gx_rec, pos_offset, stride, n, abc_host, dt, 
     gabc = torch.empty(3, dtype=torch.float64, device=lam_rec.device)
     check(lib().soax_adjoint_strided(ctypes.c_void_p(tape.data_ptr()), rl, n, sd, abc_host,
                                      float(dt), int(nsteps), int(k), rg,
-                                     ctypes.c_void_p(gabc.data_ptr()), current_stream()),
+                                     ctypes.c_void_p(gabc.data_ptr()), stream_handle()),
           "soax_adjoint_strided")
     return gabc
 

@@ -5,7 +5,7 @@ import ctypes
 import numpy as np
 
 from ._lib import check, lib
-from .particles import current_stream
+from .particles import stream_handle
 
 PER_SET, PERSISTENT, GRAPH = 0, 1, 2
 
@@ -34,7 +34,7 @@ class Batch:
         abc = np.ascontiguousarray(abc, dtype=np.float64).reshape(-1)
         assert dt.size == len(self.sets) and abc.size == 3 * len(self.sets)
         check(lib().soax_batch_step(self.handle, dt.ctypes.data, abc.ctypes.data, int(nsteps),
-                                    int(mode), current_stream()), "soax_batch_step")
+                                    int(mode), stream_handle()), "soax_batch_step")
 
     def config(self, block=0, per_thread=0, blocks_per_cu=0):
         check(lib().soax_batch_config(self.handle, block, per_thread, blocks_per_cu),

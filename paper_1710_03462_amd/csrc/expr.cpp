@@ -242,6 +242,24 @@ struct Compiled {
 std::mutex g_mu;
 std::map<std::tuple<int, std::string>, Compiled> g_cache;
 
+// What the generated source depends on: the ops with their array numbers, the
+// element types, and the streaming form.  Constants and pointers are kernel
+// arguments.  Looking a program up by it does without generating its source
+// (8 us a call) once its kernel exists.
+std::string shape_key(const ExprPlan& p) {
+  std::string k;
+  k.reserve(2 * p.nops + p.nsrc + 3);
+  for (int i = 0; i < p.nops; ++i) {
+    k.push_back(static_cast<char>(p.ops[i].op));
+    k.push_back(static_cast<char>(p.ops[i].op == kOpArray ? p.ops[i].arg : 0));
+  }
+  for (int j = 0; j < p.nsrc; ++j) k.push_back(static_cast<char>(p.src_t[j]));
+  k.push_back(static_cast<char>(p.nsrc));
+  k.push_back(static_cast<char>(p.dst_t));
+  k.push_back(static_cast<char>(p.stream));
+  return k;
+}
+
 hipError_t compile(const std::string& src, const std::string& arch, Compiled* out, std::string* log) {
   hiprtcProgram prog;
   if (hiprtcCreateProgram(&prog, src.c_str(), "soax_expr.hip", 0, nullptr, nullptr) != HIPRTC_SUCCESS) {
@@ -284,20 +302,18 @@ std::string expr_source(const ExprPlan& p) {
 }
 
 hipError_t launch_expr(const ExprPlan& p, hipStream_t s, std::string* log) {
-  std::vector<double> consts;
-  const std::string src = generate(p, &consts);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   Compiled c;
   {
     std::lock_guard<std::mutex> lock(g_mu);
-    auto key = std::make_tuple(dev, src);
+    auto key = std::make_tuple(dev, shape_key(p));
     auto it = g_cache.find(key);
     if (it == g_cache.end()) {
       hipDeviceProp_t prop;
       if ((e = hipGetDeviceProperties(&prop, dev)) != hipSuccess) return e;
-      if ((e = compile(src, prop.gcnArchName, &c, log)) != hipSuccess) return e;
+      if ((e = compile(expr_source(p), prop.gcnArchName, &c, log)) != hipSuccess) return e;
       g_cache[key] = c;
     } else {
       c = it->second;
@@ -308,7 +324,9 @@ hipError_t launch_expr(const ExprPlan& p, hipStream_t s, std::string* log) {
   for (int j = 0; j < p.nsrc; ++j) a.src[j] = p.src[j];
   a.dst = p.dst;
   a.n = p.n;
-  for (size_t j = 0; j < consts.size(); ++j) a.c[j] = consts[j];
+  int nconst = 0;  // in the order in which the source refers to them
+  for (int k = 0; k < p.nops; ++k)
+    if (p.ops[k].op == kOpConst) a.c[nconst++] = p.ops[k].value;
   size_t size = sizeof a;
   void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &a, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size,
                     HIP_LAUNCH_PARAM_END};

@@ -16,6 +16,7 @@ import torch
 
 from . import _lib
 from ._lib import check, lib
+from .particles import stream_handle
 
 ARRAY, CONST, ADD, SUB, MUL, DIV, NEG, ABS, SQRT, MIN, MAX = range(11)
 OP_NAMES = {ADD: "+", SUB: "-", MUL: "*", DIV: "/", NEG: "neg", ABS: "abs", SQRT: "sqrt",
@@ -62,10 +63,8 @@ class Expr:
 
     def program(self, index_of):
         """ctypes array of ops, ARRAY args given by index_of(key)."""
-        arr = (ExprOp * len(self.steps))()
-        for i, (op, key, value) in enumerate(self.steps):
-            arr[i] = ExprOp(op, index_of(key) if op == ARRAY else 0, float(value))
-        return arr
+        return (ExprOp * len(self.steps))(
+            *[(op, index_of(key) if op == ARRAY else 0, value) for op, key, value in self.steps])
 
     def as_tuples(self, index_of):
         return [(op, index_of(key) if op == ARRAY else 0, float(value))
@@ -104,10 +103,6 @@ def array(t):
     return Expr([(ARRAY, t, 0.0)])
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-
-
 def evaluate(dst, expr):
     """dst[i] = expr(i) over plain contiguous device tensors of one length."""
     expr = as_expr(expr)
@@ -129,7 +124,7 @@ def evaluate(dst, expr):
     src = (ctypes.c_void_p * max(len(keys), 1))(*[t.data_ptr() for t in keys])
     types = (ctypes.c_int32 * max(len(keys), 1))(*[_DTYPE_CODE[t.dtype] for t in keys])
     check(lib().soax_eval_ptrs(n, ctypes.c_void_p(dst.data_ptr()), _DTYPE_CODE[dst.dtype], src,
-                               types, len(keys), prog, len(prog), _stream()), "soax_eval_ptrs")
+                               types, len(keys), prog, len(prog), stream_handle()), "soax_eval_ptrs")
 
 
 def source(expr, dst_dtype="f64", src_dtypes=()):

@@ -22,8 +22,14 @@ NUMPY_DTYPE = {"i8": np.int8, "u8": np.uint8, "i32": np.int32, "i64": np.int64,
 MAX_PARTICLES = 2 ** 31 - 1  # records a set can hold (the C ABI's limit)
 
 
+def stream_handle():
+    """The current stream's handle as an integer, without a torch.cuda.Stream
+    object (0.3 us in place of 2.8 us of every call)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def current_stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(stream_handle())
 
 
 def params(abc=None, wrap=False):
@@ -132,7 +138,7 @@ class ParticleSet:
         old = (self._soa_store, self._aos_store)
         self._alloc(min(max(need, 2 * self.capacity), MAX_PARTICLES))
         check(lib().soax_rebind(self.handle, self.capacity, self._soa_ptrs(), self._aos_ptr(),
-                                current_stream()), "soax_rebind")
+                                stream_handle()), "soax_rebind")
         del old  # the library has copied the particles and synchronised
         if self._aosoa_store is not None:  # the move detached it; attach a larger one
             self._bind_aosoa()
@@ -153,7 +159,7 @@ class ParticleSet:
     def resize(self, n):
         """New size; particles beyond the old size are zero bytes."""
         self._ensure(int(n))
-        check(lib().soax_resize(self.handle, int(n), current_stream()), "soax_resize")
+        check(lib().soax_resize(self.handle, int(n), stream_handle()), "soax_resize")
         self._views()
 
     def reserve(self, capacity):
@@ -169,7 +175,7 @@ class ParticleSet:
         count = buf.size // self.stride
         self._ensure(self.n + count)
         check(lib().soax_push_back(self.handle, buf.ctypes.data_as(ctypes.c_void_p), count,
-                                   current_stream()), "soax_push_back")
+                                   stream_handle()), "soax_push_back")
         self._views()
 
     def record_dtype(self):
@@ -213,7 +219,7 @@ class ParticleSet:
             raise ValueError("flags must be a contiguous tensor of n elements")
         new_n = ctypes.c_int64()
         check(lib().soax_remove_flagged(self.handle, ctypes.c_void_p(flags.data_ptr()),
-                                        ctypes.byref(new_n), current_stream()),
+                                        ctypes.byref(new_n), stream_handle()),
               "soax_remove_flagged")
         self._views()
         return new_n.value
@@ -237,12 +243,12 @@ class ParticleSet:
             return key[2]
 
         prog = expr.program(index_of)
-        check(lib().soax_eval(self.handle, d, prog, len(prog), current_stream()), "soax_eval")
+        check(lib().soax_eval(self.handle, d, prog, len(prog), stream_handle()), "soax_eval")
 
     # ------------------------------------------------------------ operations
     def fill(self, seed=0, vel_mode=0, abc=None):
         p = params(abc)
-        check(lib().soax_fill(self.handle, seed, vel_mode, ctypes.byref(p), current_stream()),
+        check(lib().soax_fill(self.handle, seed, vel_mode, ctypes.byref(p), stream_handle()),
               "soax_fill")
 
     def step(self, layout, integrator, dt, nsteps, abc=None, wrap=True):
@@ -250,7 +256,7 @@ class ParticleSet:
         integ = _lib.INTEGRATORS[integrator] if isinstance(integrator, str) else integrator
         p = params(abc, wrap)
         check(lib().soax_step(self.handle, lay, integ, float(dt), int(nsteps), ctypes.byref(p),
-                              current_stream()), "soax_step")
+                              stream_handle()), "soax_step")
 
     def step_fused(self, integrator, dt, nsteps, abc=None, wrap=True):
         """nsteps SoA steps in one launch with every particle held in registers
@@ -258,7 +264,7 @@ class ParticleSet:
         integ = _lib.INTEGRATORS[integrator] if isinstance(integrator, str) else integrator
         p = params(abc, wrap)
         check(lib().soax_step_fused(self.handle, integ, float(dt), int(nsteps), ctypes.byref(p),
-                                    current_stream()), "soax_step_fused")
+                                    stream_handle()), "soax_step_fused")
 
     def step_graph(self, layout, integrator, dt, nsteps, abc=None, wrap=True):
         """The nsteps launches of step() captured once; call .launch() to replay."""
@@ -269,16 +275,16 @@ class ParticleSet:
         check(lib().soax_step_config(self.handle, lay, block, per_thread), "soax_step_config")
 
     def aos_to_soa(self):
-        check(lib().soax_aos_to_soa(self.handle, current_stream()), "soax_aos_to_soa")
+        check(lib().soax_aos_to_soa(self.handle, stream_handle()), "soax_aos_to_soa")
 
     def soa_to_aos(self):
-        check(lib().soax_soa_to_aos(self.handle, current_stream()), "soax_soa_to_aos")
+        check(lib().soax_soa_to_aos(self.handle, stream_handle()), "soax_soa_to_aos")
 
     def soa_to_aosoa(self):
-        check(lib().soax_soa_to_aosoa(self.handle, current_stream()), "soax_soa_to_aosoa")
+        check(lib().soax_soa_to_aosoa(self.handle, stream_handle()), "soax_soa_to_aosoa")
 
     def aosoa_to_soa(self):
-        check(lib().soax_aosoa_to_soa(self.handle, current_stream()), "soax_aosoa_to_soa")
+        check(lib().soax_aosoa_to_soa(self.handle, stream_handle()), "soax_aosoa_to_soa")
 
     def download_aosoa(self):
         """The tiled copy's bytes for the first ceil(n / 64) tiles."""
@@ -325,7 +331,7 @@ class StepGraph:
         self.handle = h
 
     def launch(self):
-        check(lib().soax_step_graph_launch(self.handle, current_stream()), "soax_step_graph_launch")
+        check(lib().soax_step_graph_launch(self.handle, stream_handle()), "soax_step_graph_launch")
 
     def close(self):
         if getattr(self, "handle", None) is not None and self.handle.value:
@@ -344,7 +350,7 @@ def copy(dst, src):
     nbytes = src.numel() * src.element_size()
     assert dst.numel() * dst.element_size() >= nbytes
     check(lib().soax_copy(ctypes.c_void_p(dst.data_ptr()), ctypes.c_void_p(src.data_ptr()),
-                          nbytes, current_stream()), "soax_copy")
+                          nbytes, stream_handle()), "soax_copy")
 
 
 PROBES = {"rk2": 0, "euler": 1, "read": 2, "write": 3}
@@ -363,4 +369,4 @@ def probe(pattern, pos, vel=None):
         for t in vel:
             assert t.dtype == torch.float32 and t.numel() == n
         vp = (ctypes.c_void_p * 3)(*[t.data_ptr() for t in vel])
-    check(lib().soax_probe(PROBES[pattern], pp, vp, n, current_stream()), "soax_probe")
+    check(lib().soax_probe(PROBES[pattern], pp, vp, n, stream_handle()), "soax_probe")
