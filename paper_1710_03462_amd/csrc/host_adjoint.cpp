@@ -203,7 +203,8 @@ soax_status soax_adjoint_strided(const double* tape, const double* const* lamT, 
   if (!is_finite(dt)) return fail(SOAX_E_ARG, "dt is not finite");
   if (!tape && n > 0 && nsteps > 0) return fail(SOAX_E_ARG, "tape is NULL");
   hipStream_t s = as_stream(stream);
-  const int64_t parts = std::max<int64_t>(adjoint_partials(n), 1);
+  const int tier = shift_tier(dt, abc[0], abc[1], abc[2]);
+  const int64_t parts = std::max<int64_t>(adjoint_partials(n, tier), 1);
   Partials partial;
   hipError_t e = partial.take(parts * 3 * sizeof(double), s);
   if (e != hipSuccess) return fail(SOAX_E_OOM, "device memory for partial sums: %s", hipGetErrorString(e));
@@ -283,7 +284,7 @@ soax_status soax_adjoint_noalloc(const double* tape, const double* const* lamT, 
   if (!grad_abc) return fail(SOAX_E_ARG, "grad_abc is NULL");
   if (n < 0) return fail(SOAX_E_ARG, "bad n");
   const int64_t max_n = SOAX_ADJOINT_NOALLOC_MAX_N;
-  if (n > max_n || adjoint_partials(n) * 3 * int64_t(sizeof(double)) > kNoAllocScratchBytes)
+  if (n > max_n || adjoint_partials(n, kTierAny) * 3 * int64_t(sizeof(double)) > kNoAllocScratchBytes)
     return fail(SOAX_E_RANGE,
                 "soax_adjoint_noalloc: n = %lld exceeds its fixed scratch (%lld bytes, at most "
                 "%lld particles); use soax_adjoint",

@@ -190,7 +190,7 @@ __device__ __forceinline__ void rk2_reverse(const StepAbc& p, const Trig3& t, do
   const double m0 = p.h.B * r0, m1 = p.h.C * r1, m2 = p.h.A * r2;
   g0 = fma(t.sz, m0, fma(t.cz, m1, fma(m.sz, l0, fma(m.cz, l1, g0))));
   g1 = fma(t.sx, m1, fma(t.cx, m2, fma(m.sx, l1, fma(m.cx, l2, g1))));
-  g2 = fma(t.cy, m0, fma(t.sy, m2, fma(m.cy, l0, fma(m.sy, l2, g2))));
+  g2 = fma(t.sy, m2, fma(t.cy, m0, fma(m.sy, l2, fma(m.cy, l0, g2))));
   l0 = fma(p.d.B, fma(t.cx, m1, fma(-t.sx, m2, r0)), l0);
   l1 = fma(p.d.C, fma(t.cy, m2, fma(-t.sy, m0, r1)), l1);
   l2 = fma(p.d.A, fma(t.cz, m0, fma(-t.sz, m1, r2)), l2);
@@ -451,6 +451,221 @@ __global__ __launch_bounds__(kRedBlock, 2) void adjoint_blocks_kernel(AdjointArg
   block_sum3(a.dt * g0, a.dt * g1, a.dt * g2, a.partial + 3 * static_cast<int64_t>(blockIdx.x));
 }
 
+// ------------------------------------------- small sets: a quad per particle
+//
+// Up to kQuadMax particles the kernels above leave the machine short of
+// waves: a wave is alone on its SIMD, and its time is its instruction count.
+// Here a particle's three coordinates go to three lanes of a quad (the fourth
+// repeats the first and stores nothing), which halves the instructions of a
+// step and quadruples the waves.  The field and its transpose couple the
+// coordinates cyclically,
+//   u_d = alpha_d sin x_(d+2) + beta_d cos x_(d+1),
+//   alpha = (A, B, C), beta = (C, A, B), indices modulo 3,
+// so every lane runs the same code on its own coordinate and its two
+// neighbours' values, moved within the quad.  Each component is evaluated in
+// the same order as above: the results are the same, bit for bit, but for the
+// order in which particles' parameter gradients are summed.
+
+// Lane d's value from lanes (d+1) mod 3 and (d+2) mod 3 of its quad.
+constexpr int kQuadNext = 1 | (2 << 2) | (0 << 4) | (1 << 6);
+constexpr int kQuadPrev = 2 | (0 << 2) | (1 << 4) | (2 << 6);
+
+template <int CTRL>
+__device__ __forceinline__ double quad_move(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b), CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+__device__ __forceinline__ double quad_next(double v) { return quad_move<kQuadNext>(v); }
+__device__ __forceinline__ double quad_prev(double v) { return quad_move<kQuadPrev>(v); }
+
+template <typename T>
+__device__ __forceinline__ T pick3(int d, T a, T b, T c) {
+  return d == 0 ? a : (d == 1 ? b : c);
+}
+
+// One coordinate's share of the field's coefficients, times dt/2 and dt.
+struct QuadAbc {
+  double ah, bh, ad, bd;  // alpha and beta
+  double ch, cd;          // (B, C, A): the rows of the transposed Jacobian
+  __device__ __forceinline__ QuadAbc(const StepAbc& p, int d)
+      : ah(pick3(d, p.h.A, p.h.B, p.h.C)), bh(pick3(d, p.h.C, p.h.A, p.h.B)),
+        ad(pick3(d, p.d.A, p.d.B, p.d.C)), bd(pick3(d, p.d.C, p.d.A, p.d.B)),
+        ch(pick3(d, p.h.B, p.h.C, p.h.A)), cd(pick3(d, p.d.B, p.d.C, p.d.A)) {}
+};
+
+struct Trig1 {
+  double s, c;
+};
+
+__device__ __forceinline__ double quad_field(double a, double b, const Trig1& t) {
+  return fma(a, quad_prev(t.s), b * quad_next(t.c));
+}
+
+template <int TIER>
+__device__ __forceinline__ Trig1 shift1(const Trig1& t, double d) {
+  Trig1 r;
+  trig::sincos_shift<TIER>(0.0, t.s, t.c, d, &r.s, &r.c);
+  return r;
+}
+
+// rk2_advance_to on one coordinate.
+template <int TIER, bool RENEW>
+__device__ __forceinline__ void quad_advance(const QuadAbc& p, double& x, Trig1& t) {
+  static_assert(TIER != kTierAny, "the quad kernels carry");
+  const Trig1 tm = shift1<TIER>(t, quad_field(p.ah, p.bh, t));
+  const double m = quad_field(p.ad, p.bd, tm);
+  x = x + m;
+  if (RENEW)
+    trig::sincos_fast(x, &t.s, &t.c);
+  else
+    t = shift1<TIER>(t, m);
+}
+
+// rk2_reverse on one coordinate; lane d's g is the gradient of (B, C, A)[d].
+template <int TIER>
+__device__ __forceinline__ void quad_reverse(const QuadAbc& p, const Trig1& t, double& l,
+                                             double& g) {
+  const Trig1 tm = shift1<TIER>(t, quad_field(p.ah, p.bh, t));
+  const double l1 = quad_next(l), l2 = quad_prev(l);
+  const double r = fma(tm.c, l1, -(tm.s * l2));
+  const double m = p.ch * r;
+  const double m1 = quad_next(m), m2 = quad_prev(m);
+  g = fma(t.s, m1, fma(t.c, m2, fma(tm.s, l1, fma(tm.c, l2, g))));
+  l = fma(p.cd, fma(t.c, m1, fma(-t.s, m2, r)), l);
+}
+
+constexpr int kQuadBlock = 256;
+constexpr int kQuadParticles = kQuadBlock / 4;
+
+template <int TIER>
+__global__ __launch_bounds__(kQuadBlock) void rk2_ckpt_quad_kernel(CkptArgs a) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * kQuadParticles + (threadIdx.x >> 2);
+  if (i >= a.n) return;
+  const int lane = static_cast<int>(threadIdx.x) & 3;
+  const int d = lane == 3 ? 0 : lane;
+  const bool stores = lane != 3;
+  const QuadAbc p(a.step, d);
+  const int64_t e = i * a.stride, n = a.n;
+  double x = pick3(d, a.x0[0], a.x0[1], a.x0[2])[e];
+  Trig1 t;
+  trig::sincos_fast(x, &t.s, &t.c);
+  double* tp = a.tape + i;
+  int64_t to_ckpt = 0, to_renew = kAnchor;  // steps until the next of each
+  for (int64_t left = a.nsteps; left > 0;) {
+    if (to_ckpt == 0) {
+      if (stores) {
+        st1<true>(tp + d * n, x);
+        st1<true>(tp + (3 + 2 * d) * n, t.s);
+        st1<true>(tp + (4 + 2 * d) * n, t.c);
+      }
+      tp += kTapeRows * n;
+      to_ckpt = a.k;
+    }
+    // steps up to the next checkpoint, renewal or end: all but the last carry
+    int64_t run = to_ckpt < to_renew ? to_ckpt : to_renew;
+    run = run < left ? run : left;
+    left -= run;
+    to_ckpt -= run;
+    to_renew -= run;
+    const int carried = static_cast<int>(run) - 1;  // run <= kAnchor
+    int j = 0;
+    for (; j + 4 <= carried; j += 4) {
+      quad_advance<TIER, false>(p, x, t);
+      quad_advance<TIER, false>(p, x, t);
+      quad_advance<TIER, false>(p, x, t);
+      quad_advance<TIER, false>(p, x, t);
+    }
+    for (; j < carried; ++j) quad_advance<TIER, false>(p, x, t);
+    if (to_renew == 0) {
+      quad_advance<TIER, true>(p, x, t);
+      to_renew = kAnchor;
+    } else {
+      quad_advance<TIER, false>(p, x, t);
+    }
+  }
+  if (stores) st1<true>(pick3(d, a.xT[0], a.xT[1], a.xT[2]) + e, x);
+}
+
+// adjoint_kernel with a quad per particle.  A whole piece of 20 states runs as
+// straight-line code, in which the compiler also keeps the midpoints' sines
+// and cosines (a lane keeps one coordinate's, 80 registers each way).
+template <int TIER>
+__global__ __launch_bounds__(kQuadBlock, 2) void adjoint_quad_kernel(AdjointArgs a) {
+  constexpr int KM = static_cast<int>(kAnchor);
+  __shared__ double red[3][kQuadParticles];
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * kQuadParticles + (threadIdx.x >> 2);
+  const int lane = static_cast<int>(threadIdx.x) & 3;
+  const int d = lane == 3 ? 0 : lane;
+  const QuadAbc p(a.step, d);
+  double g = 0.0;
+  if (i < a.n) {
+    const int64_t n = a.n;
+    const int64_t e = i * a.stride;
+    double l = pick3(d, a.lam[0], a.lam[1], a.lam[2])[e];
+    const double* tape = a.tape + i;
+    int64_t end = a.nsteps;                      // the piece is [begin, end)
+    int64_t c = (a.nsteps + a.k - 1) / a.k - 1;  // its segment
+    double x = 0.0;
+    Trig1 t{};
+    const auto load = [&]() {
+      const double* cp = tape + c * kTapeRows * n;
+      x = cp[d * n];
+      t = Trig1{cp[(3 + 2 * d) * n], cp[(4 + 2 * d) * n]};
+    };
+    if (a.nsteps > 0) load();
+    while (end > 0) {
+      const int64_t ck = c * a.k;
+      const int64_t cut = (end - 1) / kAnchor * kAnchor;
+      const int64_t begin = cut > ck ? cut : ck;
+      int r = static_cast<int>(ck % kAnchor);
+      for (int64_t s = ck; s < begin; ++s) {
+        r = r + 1 == KM ? 0 : r + 1;
+        if (r == 0) quad_advance<TIER, true>(p, x, t);
+        else quad_advance<TIER, false>(p, x, t);
+      }
+      const int m = static_cast<int>(end - begin);
+      end = begin;
+      c = begin == ck && c > 0 ? c - 1 : c;
+      Trig1 kept[KM];
+      if (m == KM) {
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+          if (j > 0) quad_advance<TIER, false>(p, x, t);
+          kept[j] = t;
+        }
+        load();  // the next piece's checkpoint
+#pragma unroll
+        for (int j = KM - 1; j >= 0; --j) quad_reverse<TIER>(p, kept[j], l, g);
+      } else {
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+          if (j < m) {
+            if (j > 0) quad_advance<TIER, false>(p, x, t);
+            kept[j] = t;
+          }
+        }
+        load();
+#pragma unroll
+        for (int j = KM - 1; j >= 0; --j)
+          if (j < m) quad_reverse<TIER>(p, kept[j], l, g);
+      }
+    }
+    if (lane != 3) pick3(d, a.gx[0], a.gx[1], a.gx[2])[e] = l;
+  }
+  // the workgroup's sums in a fixed tree order: lane 0 holds B's gradient,
+  // lane 1 C's and lane 2 A's
+  const int q = static_cast<int>(threadIdx.x) >> 2;
+  if (lane != 3) red[pick3(lane, 1, 2, 0)][q] = a.dt * g;
+  __syncthreads();
+  for (int s = kQuadParticles / 2; s > 0; s >>= 1) {
+    if (q < s && lane != 3) red[lane][q] += red[lane][q + s];
+    __syncthreads();
+  }
+  if (threadIdx.x < 3) a.partial[3 * static_cast<int64_t>(blockIdx.x) + threadIdx.x] = red[threadIdx.x][0];
+}
+
 // One thread's share of the partial sums (every kSumBlock-th triple), in
 // ascending order.  The loads of kSumBatch triples leave before the first
 // addition: one workgroup does the whole sum, which otherwise waits out one
@@ -525,10 +740,27 @@ __global__ __launch_bounds__(kRedBlock) void sqdist_kernel(LossArgs a) {
 
 namespace {
 
+// Particles up to which a quad of lanes takes each (steps whose shifts are
+// at most 1/8): up to 2^15 the quads' waves are at most two to a SIMD.  us for
+// forward, loss and adjoint of 160 steps, k = 20, and of 130 steps with
+// dt = 1e-2, k = 16, one lane per particle -> quads: 1000 particles 86 -> 49
+// and 122 -> 68, 16000 88 -> 51 and 126 -> 71, 32000 90 -> 72 and 128 -> 97;
+// 50000 91 -> 116 and 129 -> 161.
+constexpr int64_t kQuadMax = 1 << 15;
+
+bool quad_case(int64_t n, int tier) { return n <= kQuadMax && tier != kTierAny; }
+
+int64_t quad_blocks(int64_t n) { return (n + kQuadParticles - 1) / kQuadParticles; }
+
 template <int TIER>
 void forward_launch(const CkptArgs& a, hipStream_t s) {
   const int64_t grid = (a.n + 255) / 256;
   if constexpr (TIER != kTierAny) {
+    if (quad_case(a.n, TIER)) {
+      hipLaunchKernelGGL(rk2_ckpt_quad_kernel<TIER>, dim3(quad_blocks(a.n)), dim3(kQuadBlock), 0, s,
+                         a);
+      return;
+    }
     if (a.k % kAnchor == 0 && a.nsteps % kAnchor == 0) {
       hipLaunchKernelGGL(rk2_ckpt_blocks_kernel<TIER>, dim3(grid), dim3(256), 0, s, a);
       return;
@@ -539,7 +771,9 @@ void forward_launch(const CkptArgs& a, hipStream_t s) {
 
 template <int TIER>
 void adjoint_launch(const AdjointArgs& a, int64_t grid, hipStream_t s) {
-  if (a.k % kAnchor == 0 && a.nsteps % kAnchor == 0)
+  if (quad_case(a.n, TIER))
+    hipLaunchKernelGGL(adjoint_quad_kernel<TIER>, dim3(grid), dim3(kQuadBlock), 0, s, a);
+  else if (a.k % kAnchor == 0 && a.nsteps % kAnchor == 0)
     hipLaunchKernelGGL(adjoint_blocks_kernel<TIER>, dim3(grid), dim3(kRedBlock), 0, s, a);
   else if (a.k <= 10)
     hipLaunchKernelGGL((adjoint_kernel<10, 0, 10, TIER>), dim3(grid), dim3(kRedBlock), 0, s, a);
@@ -560,10 +794,12 @@ hipError_t launch_rk2_forward_ckpt(const CkptArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int64_t adjoint_partials(int64_t n) { return (n + kRedBlock - 1) / kRedBlock; }
+int64_t adjoint_partials(int64_t n, int tier) {
+  return quad_case(n, tier) ? quad_blocks(n) : (n + kRedBlock - 1) / kRedBlock;
+}
 
 hipError_t launch_adjoint(const AdjointArgs& a, hipStream_t s) {
-  const int64_t grid = adjoint_partials(a.n);
+  const int64_t grid = adjoint_partials(a.n, a.tier);
   if (grid > 0) {
     switch (a.tier) {
       case kTierSmall: adjoint_launch<kTierSmall>(a, grid, s); break;

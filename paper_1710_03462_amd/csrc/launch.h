@@ -255,7 +255,7 @@ struct AdjointArgs {
   int32_t tier;  // shift_tier of dt and the amplitudes
 };
 // number of per-block partial sums launch_adjoint needs (3 doubles each)
-int64_t adjoint_partials(int64_t n);
+int64_t adjoint_partials(int64_t n, int tier);
 hipError_t launch_adjoint(const AdjointArgs& a, hipStream_t s);
 
 struct LossArgs {

@@ -44,6 +44,24 @@ def test_pieces_agree_bit_for_bit_and_with_the_oracle(ref, dt, nsteps):
     assert np.all(np.abs(want[3] - rgabc) <= 1e-6 * np.abs(rgabc).max())
 
 
+@pytest.mark.parametrize("dt", [5e-3, 2e-2])
+@pytest.mark.parametrize("nsteps,k", [(1, 1), (20, 20), (40, 20), (61, 16), (61, 7), (100, 33)])
+def test_a_small_set_equals_its_part_of_a_large_one(dt, nsteps, k):
+    # up to 2^15 particles a quad of lanes takes each; a particle's results do
+    # not depend on it, nor do the sums but for their order
+    n = (1 << 15) + 1
+    x0, target = (torch.from_numpy(a).cuda() for a in si.adjoint_inputs(n, seed=k))
+    large = _run(x0, target, dt, nsteps, k)
+    total = np.zeros(3)
+    for part in (slice(0, n - 1), slice(n - 1, n)):
+        small = _run(x0[:, part].contiguous(), target[:, part].contiguous(), dt, nsteps, k)
+        assert np.array_equal(small[0], large[0][:, part])
+        assert np.array_equal(small[2], large[2][:, part])
+        total += small[3]
+    # 2^15 terms of at most a few units each, summed twice in different orders
+    assert np.abs(total - large[3]).max() <= 1e-12 * n
+
+
 @pytest.mark.parametrize("parts", [1, 1023, 1024, 1025, 8192, 8193, 16384])
 def test_partial_sums_of_every_batch_remainder(parts):
     # one partial sum per 256 particles; whole numbers, so every order of
