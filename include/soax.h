@@ -205,9 +205,9 @@ soax_status soax_step_fused(soax_set* set, int32_t integrator, double dt, int64_
  * (64..1024, multiple of 64) and particles per thread (1, 2 or 4; SoA only).
  * 0 restores the default: 128 threads (256 for the AoS layouts; the staged
  * AoS step of a set of at least 128 MB of records picks tile and threads by
- * the record size) and one particle per thread; two particles per thread for RK4 steps on SoA arrays
- * that are 16-byte aligned and span at least 128 MB (positions and
- * velocities).
+ * the record size) and one particle per thread; 64 threads and, where the
+ * arrays are 16-byte aligned, two particles per thread for RK4 steps on SoA
+ * arrays of at least 128 MB (positions and velocities).
  * Heun and RK4 steps, and any step whose positions or velocities are 8-byte
  * elements, take at most two per thread.  Results do not depend on the
  * shape.

@@ -158,91 +158,8 @@ __global__ __launch_bounds__(1024) void soa_step_kernel(SoaStepArgs a) {
   }
 }
 
-// The RK4 step on streaming sets.  Each workgroup takes two consecutive runs
-// of blockDim.x * VEC particles and issues the second run's position loads
-// before the first run's arithmetic, so that they are in flight while it
-// computes.  RK4 issues 1.6x the fp64 instructions of RK2 and its arithmetic and memory
-// traffic overlap less; this order made it about 3% faster at 1e8 particles
-// (1.28 against 1.32 ms, interleaved runs), while it made RK2 and Heun no
-// faster.  The last, incomplete pair of runs is stepped one particle per
-// thread with the same arithmetic, so the results do not depend on the
-// shape.
-template <typename PT, typename VT, int VEC, int TIER>
-__global__ __launch_bounds__(1024) void soa_rk4_two_runs_kernel(SoaStepArgs a) {
-  const StepAbc& p = a.abc;
-  PT* px = static_cast<PT*>(a.pos[0]);
-  PT* py = static_cast<PT*>(a.pos[1]);
-  PT* pz = static_cast<PT*>(a.pos[2]);
-  VT* vx = static_cast<VT*>(a.vel[0]);
-  VT* vy = static_cast<VT*>(a.vel[1]);
-  VT* vz = static_cast<VT*>(a.vel[2]);
-  const int64_t run = static_cast<int64_t>(blockDim.x) * VEC;
-  const int64_t fa = static_cast<int64_t>(blockIdx.x) * 2 * run;
-  const int64_t fb = fa + run;
-  const int e = static_cast<int>(threadIdx.x) * VEC;
-  if (fb + run <= a.n) {
-    PT xa[VEC], ya[VEC], za[VEC], xb[VEC], yb[VEC], zb[VEC];
-    step_ld<true, PT, VEC>(px, fa, run, e, xa);
-    step_ld<true, PT, VEC>(py, fa, run, e, ya);
-    step_ld<true, PT, VEC>(pz, fa, run, e, za);
-    step_ld<true, PT, VEC>(px, fb, run, e, xb);
-    step_ld<true, PT, VEC>(py, fb, run, e, yb);
-    step_ld<true, PT, VEC>(pz, fb, run, e, zb);
-    VT u[VEC], v[VEC], w[VEC];
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-      u[j] = v[j] = w[j] = VT(0);
-      update_particle<kRk4Abc, PT, VT, TIER>(xa[j], ya[j], za[j], u[j], v[j], w[j], VT(0), VT(0),
-                                             VT(0), a.dt, p, a.wrap);
-    }
-    step_st<true, PT, VEC>(px, fa, run, e, xa);
-    step_st<true, PT, VEC>(py, fa, run, e, ya);
-    step_st<true, PT, VEC>(pz, fa, run, e, za);
-    step_st<true, VT, VEC>(vx, fa, run, e, u);
-    step_st<true, VT, VEC>(vy, fa, run, e, v);
-    step_st<true, VT, VEC>(vz, fa, run, e, w);
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-      u[j] = v[j] = w[j] = VT(0);
-      update_particle<kRk4Abc, PT, VT, TIER>(xb[j], yb[j], zb[j], u[j], v[j], w[j], VT(0), VT(0),
-                                             VT(0), a.dt, p, a.wrap);
-    }
-    step_st<true, PT, VEC>(px, fb, run, e, xb);
-    step_st<true, PT, VEC>(py, fb, run, e, yb);
-    step_st<true, PT, VEC>(pz, fb, run, e, zb);
-    step_st<true, VT, VEC>(vx, fb, run, e, u);
-    step_st<true, VT, VEC>(vy, fb, run, e, v);
-    step_st<true, VT, VEC>(vz, fb, run, e, w);
-    return;
-  }
-  const int64_t end = min(fa + 2 * run, a.n);
-  for (int64_t i = fa + threadIdx.x; i < end; i += blockDim.x) {
-    PT x = px[i], y = py[i], z = pz[i];
-    VT u = VT(0), v = VT(0), w = VT(0);
-    update_particle<kRk4Abc, PT, VT, TIER>(x, y, z, u, v, w, VT(0), VT(0), VT(0), a.dt, p,
-                                           a.wrap);
-    px[i] = x;
-    py[i] = y;
-    pz[i] = z;
-    vx[i] = u;
-    vy[i] = v;
-    vz[i] = w;
-  }
-}
-
 template <int INTEG, typename PT, typename VT, int TIER, bool STREAM>
 hipError_t soa_step_launch(int vec, int64_t grid, int block, const SoaStepArgs& a, hipStream_t s) {
-  if constexpr (INTEG == kRk4Abc && STREAM) {
-    // grid counts runs of block * vec particles; one workgroup per two runs
-    const int64_t pairs = (grid + 1) / 2;
-    if (vec == 1)
-      hipLaunchKernelGGL((soa_rk4_two_runs_kernel<PT, VT, 1, TIER>), dim3(pairs), dim3(block), 0,
-                         s, a);
-    else
-      hipLaunchKernelGGL((soa_rk4_two_runs_kernel<PT, VT, 2, TIER>), dim3(pairs), dim3(block), 0,
-                         s, a);
-    return hipGetLastError();
-  }
   if constexpr (INTEG == kHeunAbc || INTEG == kRk4Abc) {
     // one or two particles per thread (the host caps vec at 2 for these)
     if (vec == 1)

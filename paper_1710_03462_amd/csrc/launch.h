@@ -222,7 +222,7 @@ hipError_t launch_stream_probe(int pattern, const ProbeArgs& a, hipStream_t s);
 
 // Position-like arrays (x0, xT, lam, gx) are read at element i * stride:
 // stride 1 for SoA arrays, the record stride in doubles for positions kept
-// inside AoS records.  The tape is always [segment][3][n].
+// inside AoS records.  The tape is always [segment][9][n].
 struct CkptArgs {
   const double* x0[3];
   double* xT[3];

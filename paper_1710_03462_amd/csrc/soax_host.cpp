@@ -226,11 +226,15 @@ soax_status soax_step(soax_set* set, int32_t layout, int32_t integrator, double 
     a.wrap = wrap;
     // one particle per thread in workgroups of 128, except for RK4 on sets
     // that stream through HBM: two consecutive particles (16-byte position
-    // accesses).  Measured at 1e8 particles, ms per step in (threads,
-    // particles per thread): RK2 0.967 (128,1), 1.045 (64,1), 0.978 (256,1),
-    // 1.020 (64,2), 1.066 (128,2), 1.080 (512,2); Heun the same within 1%;
-    // RK4, bound by its arithmetic, 1.180 (128,1), 1.152 (128,2), 1.161
-    // (64,2); Euler 0.887 (128,1), 0.944 (64,1), 0.915 (256,1), 1.000
+    // accesses) in workgroups of 64.  Measured at 1e8 particles, ms per step
+    // in (threads, particles per thread): RK2 0.962 (128,1), 0.961 (256,1),
+    // 1.011 (64,2), 1.033 (128,2), 1.041 (64,1), 1.094 (512,2); Heun the same
+    // within 1%; RK4, bound by its arithmetic, 1.150 (64,2), 1.157 (128,2),
+    // 1.154 (256,2), 1.179 (128,1), 1.186 (64,1), and with 8-byte velocities
+    // and 6e7 particles 0.735 (64,2) against 0.770 (256,2) (RK2 there 0.713
+    // (128,1), 0.740 (64,2)).  Two runs of (128,2) in one workgroup, the
+    // second's positions loaded before the first's arithmetic, took RK4 1.150
+    // and 0.812.  Euler 0.887 (128,1), 0.944 (64,1), 0.915 (256,1), 1.000
     // (128,2).  Cache-resident sets are bound by latency and keep one.
     const bool wide = integrator == SOAX_RK4_ABC &&
                       set->n * soa_step_bytes(integrator, L.f[fp].es, L.f[fv].es) >= kStreamBytes;
@@ -241,7 +245,7 @@ soax_status soax_step(soax_set* set, int32_t layout, int32_t integrator, double 
     // lines: measured 3x slower at 1e8, so 8-byte positions or velocities
     // take at most two
     if (vec > 2 && (L.f[fp].es == 8 || L.f[fv].es == 8)) vec = 2;
-    const int block = set->block[SOAX_SOA] ? set->block[SOAX_SOA] : 128;
+    const int block = set->block[SOAX_SOA] ? set->block[SOAX_SOA] : (wide ? 64 : 128);
     for (int64_t k = 0; k < nsteps; ++k)
       HIP_TRY(launch_soa_step(integrator, L.f[fp].dtype, L.f[fv].dtype, vec, block, a, s),
               "SoA step launch");
