@@ -156,8 +156,8 @@ soax_status per_set_step(soax_batch* b, const double* dt, const double* abc, hip
     a.abc = step_abc(AbcParams{abc[3 * i], abc[3 * i + 1], abc[3 * i + 2]}, dt[i]);
     a.wrap = 1;
     // one particle per thread, 128 threads: the faster shape for this mode's
-    // mostly cache-resident sets (two per thread in 64 threads took 174 ms
-    // against 150 ms for 100 steps of the 256-set batch)
+    // mostly cache-resident sets (100 steps of the 256-set batch take 145 ms;
+    // two per thread in 64 threads took 1.16x as long)
     HIP_TRY(launch_soa_step(kRk2Abc, kF64, b->vel_t, 1, 128, a, s), "per-set step launch");
   }
   return SOAX_OK;
@@ -225,8 +225,8 @@ soax_status soax_batch_create(soax_set* const* sets, int32_t nsets, soax_batch**
   // Two consecutive particles per thread (16-byte position accesses) where
   // the batch streams through HBM, one where it stays in the caches and is
   // bound by latency.  us per step in workgroups of 256, one / two per thread:
-  // 493 / 470 for 256 sets of 4.6e7 particles in all, 75 / 71 for 100 sets of
-  // 6.8e6 (246 MB), 7.8 / 8.6 for 64 sets of 4e5.
+  // 463 / 456 for 256 sets of 4.6e7 particles in all, 71 / 71 for 100 sets of
+  // 6.8e6 (246 MB), 6.8 / 8.5 for 64 sets of 4e5.
   if (total * soa_step_bytes(kRk2Abc, sizeof(double), dtype_size(vel_t)) >= kStreamBytes)
     b->per_thread = 2;
   int dev = 0;

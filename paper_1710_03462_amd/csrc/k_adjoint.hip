@@ -2,8 +2,8 @@
 // ABC field: forward with checkpoints, the discrete adjoint with
 // recomputation, and a squared-distance loss.
 //
-// One thread owns one particle for the whole time loop (the state stays in
-// registers).  The adjoint walks the checkpoint segments backwards; for each
+// One thread owns one particle (in small sets a quad of lanes does, see below)
+// for the whole time loop; the state stays in registers.  The adjoint walks the checkpoint segments backwards; for each
 // segment it recomputes the states from the checkpoint, keeping every state's
 // sines and cosines (in registers, indexed by compile-time constants through
 // fully unrolled loops so that they never touch scratch memory, and in LDS),
@@ -24,9 +24,7 @@ namespace soax {
 
 namespace {
 
-constexpr int kRedBlock = kAdjointBlock;  // workgroup size of every reducing kernel
-
-
+constexpr int kRedBlock = kAdjointBlock;  // workgroup size of every reducing kernel but the quads'
 
 // Rows of one checkpoint on the tape: the position and the sines and cosines
 // the forward evaluated at it.
@@ -229,8 +227,8 @@ __device__ __forceinline__ void opaque(Trig3& t) {
 // The sines and cosines of the states 0 .. K - 1 of a (sub-)segment, written
 // by the recomputation and read by the reverse sweep with compile-time
 // indices (the sweep used to carry them back from state to state, 36 more
-// instructions a step): the first L states in LDS, one 16-byte pair per coordinate and
-// thread, the others in registers.
+// instructions a step): the first L states in LDS, one 16-byte pair per
+// coordinate and thread, the others in registers.
 //
 // The reverse sweep also needs each step's midpoint values, which the
 // recomputation has had, and the compiler would rather keep those too than
@@ -275,8 +273,7 @@ constexpr int kLdsStates = 6;
 // 160 steps, forward and loss included, before -> now: k = 16 7.28 -> 5.71 ms,
 // k = 10 7.68 -> 5.24, k = 5 7.86 -> 5.69, k = 32 9.14 -> 6.18, and with
 // shifts beyond 1/64, which used to reduce every state in full, 11.7 -> 5.9.
-// A segment is cut
-// into pieces of at most KM states that do not cross a renewal point, so that
+// A segment is cut into pieces of at most KM states that do not cross a renewal point, so that
 // a piece's recomputation only carries; the steps from the checkpoint to a
 // later piece's first state are taken one by one.  KM: states kept, the first
 // L of them in LDS; REUSE: as in KeptTrig.

@@ -74,8 +74,8 @@ __device__ __forceinline__ void batch_tile(const BatchSet& S, int64_t t, int32_t
 // uniform over the workgroup, which works on one tile at a time).  MAXT, the
 // largest tier of any set in the batch, leaves the paths of larger tiers out
 // of the kernel: the unbounded tier's full-reduction fallback alone raises
-// the kernel's registers (at two particles per thread from about 72 to 100
-// VGPRs, seven resident waves per SIMD to four).
+// the kernel's registers (at two particles per thread from 75 to 93 VGPRs, six
+// resident waves per SIMD to five).
 template <typename VT, int PPT, int MAXT>
 __device__ __forceinline__ void batch_tile_any(const BatchSet& S, int64_t t, int32_t tile) {
   if (MAXT == kTierSmall || S.tier == kTierSmall)
