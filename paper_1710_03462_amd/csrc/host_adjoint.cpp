@@ -33,6 +33,22 @@ extern "C" {
 // graph) take the pool.
 namespace {
 
+// Querying or making an event would invalidate a capture that another thread
+// has open in the global mode; neither touches a capturing stream here.
+class RelaxedCapture {
+ public:
+  RelaxedCapture() { on_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+  ~RelaxedCapture() {
+    if (on_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;  // the thread's own, once exchanged
+  bool on_;
+};
+
 constexpr int kMaxDevices = 64;
 
 class Partials {
@@ -73,6 +89,7 @@ hipError_t Partials::take(size_t bytes, hipStream_t s) {
   if (bytes > kKeptBytes || dev >= kMaxDevices || hipStreamIsCapturing(s, &cap) != hipSuccess ||
       cap != hipStreamCaptureStatusNone)
     return hipMallocAsync(&p_, bytes, s);
+  RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lock(mu_);
   Buffer* pick = nullptr;
   Buffer* place = nullptr;  // free

@@ -1,11 +1,13 @@
 """The partial sums of the loss and the adjoint on many streams and threads
 at once: every call gets its own sums."""
+import ctypes
 import threading
 
 import pytest
 
 torch = pytest.importorskip("torch")
 soax = pytest.importorskip("paper_1710_03462_amd")
+from paper_1710_03462_amd import _lib  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +55,42 @@ def test_many_threads(shared):
     for t in threads:
         t.join()
     assert not wrong
+
+
+@pytest.mark.parametrize("n", [300, 100_000])
+def test_beside_another_threads_capture(n):
+    # a capture in the global mode is invalidated by unsafe calls of any
+    # thread; the C call with memory of the caller's makes none
+    zero = torch.zeros((3, n), dtype=torch.float64, device="cuda")
+    x, want = _input(7, n)
+    y = torch.zeros(64, device="cuda")
+    loss = torch.zeros(16, dtype=torch.float64, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    dev = torch.cuda.current_device()
+    rows = [(ctypes.c_void_p * 3)(*(t[d].data_ptr() for d in range(3))) for t in (x, zero)]
+    codes = []
+
+    def work(first, times):
+        torch.cuda.set_device(dev)
+        for i in range(first, first + times):
+            codes.append(_lib.lib().soax_sqdist_loss(
+                rows[0], rows[1], n, None, ctypes.c_void_p(loss.data_ptr() + 8 * i),
+                ctypes.c_void_p(s.cuda_stream)))
+
+    work(0, 4)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        y.add_(1.0)
+        t = threading.Thread(target=work, args=(4, 8))
+        t.start()
+        t.join()
+        y.add_(1.0)
+    for k in range(3):
+        g.replay()
+        work(12 + k, 1)
+        torch.cuda.synchronize()
+        assert y.unique().tolist() == [2.0 * (k + 1)]
+    assert codes == [0] * 15
+    assert loss.tolist() == [want] * 15 + [0.0]
