@@ -2,8 +2,8 @@
 the polynomial coefficients by Remez's exchange method.
 
 pi is computed to 120 decimal digits with Machin's formula in integer
-arithmetic; pi/2 is the sum of two doubles, the nearest one and the remainder
-rounded.  The polynomials minimise the largest error of the function they
+arithmetic; pi/2 is the sum of three doubles, each the nearest one to what the
+ones before it leave.  The polynomials minimise the largest error of the function they
 stand for over their interval (E. Ya. Remez, 1934): with f given by its
 rational Taylor series, each round solves w(x_i) (P(x_i) - f(x_i)) =
 (-1)^i E at the current points exactly, and moves the points to the extrema
@@ -112,8 +112,10 @@ def main():
     pi = pi_fraction()
     half_pi = pi / 2
     hi = Fraction(float(half_pi))
-    lo = float(half_pi - hi)
-    for name, v in (("kPio2Hi", float(hi)), ("kPio2Lo", lo), ("kTwoOverPi", float(1 / half_pi))):
+    lo = Fraction(float(half_pi - hi))
+    tail = float(half_pi - hi - lo)
+    for name, v in (("kPio2Hi", float(hi)), ("kPio2Lo", float(lo)), ("kPio2Tail", tail),
+                    ("kTwoOverPi", float(1 / half_pi))):
         print(f"constexpr double {name} = {v.hex()};  // {v!r}")
     # sin r = r + r w P(w), cos r = 1 - w/2 + w^2 Q(w), w = r^2, |r| <= pi/4
     # (a little more for the rounding of the quadrant): relative and absolute

@@ -4,11 +4,14 @@
 // stay within a few box edges of the origin, so the full-range reduction of
 // the device math library (Payne-Hanek) is replaced for |x| <= 2^19 by
 //   k = nearest integer to x * 2/pi,  r = x - k*pi/2  with pi/2 as the sum
-//   of two doubles, one fma each.  The first is exact: pi/2's leading double
+//   of three doubles, one fma each.  The first is exact: pi/2's leading double
 //   is a multiple of 2^-52, so is x (or k is 0 or 1 and the difference is a
-//   multiple of 2^-53), and |r| < 1 leaves at most 53 bits.  The second is
-//   then the reduction's only rounding.  k comes from one fma that adds
-//   1.5 * 2^52, whose low word holds k.
+//   multiple of 2^-53), and |r| < 1 leaves at most 53 bits.  The second rounds
+//   once, and the third adds k 2^-109, which is below that rounding except
+//   where x is next to a multiple of pi/2 and r is tiny: there it is what
+//   keeps r's relative error at one ulp (two doubles alone are up to 5e4 ulp
+//   off at the doubles nearest k pi/2, k < 2^18.4).  k comes from one fma that
+//   adds 1.5 * 2^52, whose low word holds k.
 // The sine and cosine of |r| <= pi/4 are minimax polynomials of degree 13 and
 // 14 (gen_trig_constants.py; largest errors 3.4e-18 of the sine and 4.7e-20),
 // evaluated by Horner's rule.  The quadrant k mod 4 picks and signs the
@@ -29,14 +32,18 @@
 // back to sincos_fast(x + d) (see the tiers below).  The shift uses the exact
 // sum x + d, which differs from the rounded sum by at most half an ulp of x.
 //
-// The field integrators are bound by fp64 issue or close to it.  Against three
-// reduction constants, Taylor series two terms longer and angle addition:
-// 50 fused RK2 steps of 1e7 particles 2.44 -> 2.24 ms, RK4 0.926 -> 0.886 ms
-// per 10 steps of 6e6, the streaming RK2 step 1.013 -> 0.973 ms at 1e8,
-// forward and adjoint of 1e7 x 200 steps 19.2 -> 18.1 ms.
+// The field integrators are bound by fp64 issue or close to it.  Against a
+// quadrant by rint, Taylor series two terms longer and angle addition, with
+// pi/2 in two constants: 50 fused RK2 steps of 1e7 particles 2.44 -> 2.24 ms,
+// RK4 0.926 -> 0.886 ms per 10 steps of 6e6, the streaming RK2 step 1.013 ->
+// 0.973 ms at 1e8, forward and adjoint of 1e7 x 200 steps 19.2 -> 18.1 ms.
+// The third constant costs about 1% of that again (1.93 -> 1.96, 0.832 ->
+// 0.838, 0.958 -> 0.965 and 14.53 -> 14.54 ms beside later changes).
 //
-// Measured on the host against glibc over seeded arguments: within 2 ulp for
-// |x| up to 2^19, and the shifted forms within one ulp of 1 in absolute error.
+// Measured on the host: within 2 ulp for |x| up to 2^19, against glibc over
+// seeded arguments and against integers of 400 bits at the doubles next to the
+// multiples of pi/2, and the shifted forms within one ulp of 1 in absolute
+// error.
 // The GPU's results equal the host build's bit for bit (both are chains of
 // correctly rounded fmas).
 #pragma once
@@ -48,6 +55,7 @@ namespace trig {
 
 constexpr double kPio2Hi = 0x1.921fb54442d18p+0;
 constexpr double kPio2Lo = 0x1.1a62633145c07p-54;
+constexpr double kPio2Tail = -0x1.f1976b7ed8fbcp-110;
 constexpr double kTwoOverPi = 0x1.45f306dc9c883p-1;
 constexpr double kRoundMagic = 0x1.8p52;
 constexpr double kFastMax = 0x1p19;
@@ -109,7 +117,7 @@ __host__ __device__ __forceinline__ bool beyond_fast(double x) { return !(fabs(x
 __host__ __device__ __forceinline__ void sincos_core(double x, double* s, double* c) {
   const double t = fma(x, kTwoOverPi, kRoundMagic);
   const double k = t - kRoundMagic;
-  const double r = fma(-k, kPio2Lo, fma(-k, kPio2Hi, x));
+  const double r = fma(-k, kPio2Tail, fma(-k, kPio2Lo, fma(-k, kPio2Hi, x)));
   const double w = r * r;
   double ps, pc;
   sin_cos_series(w, ps, pc);
