@@ -173,8 +173,10 @@ __global__ __launch_bounds__(256) void rk2_ckpt_blocks_kernel(CkptArgs a) {
 //   r = (cos x_m lam_1 - sin x_m lam_2, ...),  m = (dt/2) (B, C, A) r,
 //   g/dt += G(xm)^T lam+ + G(x)^T m,
 //   lam  = lam+ + dt (B, C, A) (r + (cos x m_1 - sin x m_2, ...))
-// so that every sum is a chain of fused multiply-adds.  (x, y, z) is read by
-// kTierAny alone.
+// so that every sum is a chain of fused multiply-adds.  A step's four terms of
+// g are summed by themselves, smallest first, and added with one rounding of
+// g's size: taken into g one by one they round it four times a step.
+// (x, y, z) is read by kTierAny alone.
 template <int TIER>
 __device__ __forceinline__ void rk2_reverse(const StepAbc& p, const Trig3& t, double x, double y,
                                             double z, double& l0, double& l1, double& l2,
@@ -186,9 +188,9 @@ __device__ __forceinline__ void rk2_reverse(const StepAbc& p, const Trig3& t, do
   const double r1 = fma(m.cy, l2, -(m.sy * l0));
   const double r2 = fma(m.cz, l0, -(m.sz * l1));
   const double m0 = p.h.B * r0, m1 = p.h.C * r1, m2 = p.h.A * r2;
-  g0 = fma(t.sz, m0, fma(t.cz, m1, fma(m.sz, l0, fma(m.cz, l1, g0))));
-  g1 = fma(t.sx, m1, fma(t.cx, m2, fma(m.sx, l1, fma(m.cx, l2, g1))));
-  g2 = fma(t.sy, m2, fma(t.cy, m0, fma(m.sy, l2, fma(m.cy, l0, g2))));
+  g0 += fma(m.sz, l0, fma(m.cz, l1, fma(t.sz, m0, t.cz * m1)));
+  g1 += fma(m.sx, l1, fma(m.cx, l2, fma(t.sx, m1, t.cx * m2)));
+  g2 += fma(m.sy, l2, fma(m.cy, l0, fma(t.sy, m2, t.cy * m0)));
   l0 = fma(p.d.B, fma(t.cx, m1, fma(-t.sx, m2, r0)), l0);
   l1 = fma(p.d.C, fma(t.cy, m2, fma(-t.sy, m0, r1)), l1);
   l2 = fma(p.d.A, fma(t.cz, m0, fma(-t.sz, m1, r2)), l2);
@@ -381,10 +383,13 @@ __global__ __launch_bounds__(kRedBlock) void adjoint_any_kernel(AdjointArgs a) {
 // 1e7 particles x 200 steps, k = 20, with the loss and the forward: 18.2 ms
 // before the states' sines were kept, the sums fused and the carried
 // displacement left unrounded, 14.6 ms with them (adjoint 13.3 -> 9.0 ms;
-// 136 instructions per particle-step, 203 before).  One wave per SIMD with
-// 512 registers and more midpoints kept: 15.0 ms.  Errors against an 80-bit
-// reference, 2e4 particles: grad_x0 1.6e-15 (1.8e-15 before), xT 7.2e-16
-// (7.2e-16).
+// 136 instructions per particle-step, 203 before), and 14.7 with a step's
+// gradient terms summed before they reach the running sum (three more).  One
+// wave per SIMD with 512 registers and more midpoints kept: 15.0 ms against
+// the 14.6.  Errors against an 80-bit reference, before -> now: grad_x0
+// 1.8e-15 -> 1.6e-15 and xT 7.2e-16 -> 7.2e-16 of 2e4 particles,
+// dL/d(A,B,C) of 24 sets of 64 particles 8.8e-16 -> 8.1e-16 (130 steps of
+// 1e-2: 6.3e-16 -> 5.3e-16), of 3 sets of 33000 1.2e-16 -> 0.9e-16.
 //
 // adjoint_kernel when k and nsteps are multiples of kAnchor: every segment's
 // length is then a multiple of kAnchor too, and every block of kAnchor states
@@ -529,7 +534,7 @@ __device__ __forceinline__ void quad_reverse(const QuadAbc& p, const Trig1& t, d
   const double r = fma(tm.c, l1, -(tm.s * l2));
   const double m = p.ch * r;
   const double m1 = quad_next(m), m2 = quad_prev(m);
-  g = fma(t.s, m1, fma(t.c, m2, fma(tm.s, l1, fma(tm.c, l2, g))));
+  g += fma(tm.s, l1, fma(tm.c, l2, fma(t.s, m1, t.c * m2)));
   l = fma(p.cd, fma(t.c, m1, fma(-t.s, m2, r)), l);
 }
 
