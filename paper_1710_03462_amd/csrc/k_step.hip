@@ -566,7 +566,7 @@ __device__ __forceinline__ void scatter_size(const XposeArgs& t, int b, int e, i
 // its array, a block of arrays of one element size at a time (uniform across
 // the workgroup), so consecutive lanes store consecutive elements.
 template <bool ALIGNED, bool STREAM>
-__global__ __launch_bounds__(384) void aos_to_soa_kernel(const XposeArgs* __restrict__ tp,
+__global__ __launch_bounds__(256) void aos_to_soa_kernel(const XposeArgs* __restrict__ tp,
                                                          int64_t n, int tile) {
   extern __shared__ uint4 lds_u4[];
   char* lds = reinterpret_cast<char*>(lds_u4);
@@ -1043,30 +1043,25 @@ static int xpose_tile(int stride) {
 hipError_t launch_xpose(bool to_soa, const XposeArgs& host, const XposeArgs* dev,
                             hipStream_t s) {
   if (host.n == 0) return hipSuccess;
-  const bool stream = host.n * host.stride >= kStreamBytes;
-  int tile = xpose_tile(host.stride), threads = 256;
-  // AoS -> SoA of records that stream: more threads than records, so that a
-  // thread stages two or three 16-byte chunks instead of three to five and the
-  // stores to the arrays start earlier.  us per 2.4 GB of records, 256 records
-  // and threads -> this rule: 40 bytes 801 -> 775, 48 736 -> 694, 56 778 -> 741,
-  // 72 811 -> 761, 80 748 -> 720, 88 844 -> 826, 144 846 -> 794; smaller
-  // records lose (24 bytes 744 -> 935, 32 782 -> 818), and SoA -> AoS, whose
-  // gather is one record per thread, loses at every size.
-  if (to_soa && stream && host.stride >= 40 && host.stride <= 256) {
-    tile = host.stride < 72 ? 256 : 128;
-    threads = host.stride < 72 ? 384 : 320;
-  }
+  // One record per thread in both directions.  More threads than records (384
+  // on 256 below 72 bytes, 320 on 128 from there on) make AoS -> SoA of records
+  // that stream 2 to 6% faster on a card that writes 6.2 TB/s (80 bytes 748 ->
+  // 720 us per 2.4 GB) but 3% slower for records of 4-byte arrays (152 bytes
+  // 824 -> 849 us) and, on a card that writes 7.1 TB/s, for 80 bytes too (the
+  // round trip 1412 -> 1437 us).
+  const int tile = xpose_tile(host.stride);
   const int64_t grid = (host.n + tile - 1) / tile;
   const size_t lds = (static_cast<size_t>(tile) * host.stride + 15) & ~static_cast<size_t>(15);
+  const bool stream = host.n * host.stride >= kStreamBytes;
 #define SOAX_XPOSE(KER)                                                                       \
   if (host.aligned && stream)                                                                 \
-    hipLaunchKernelGGL((KER<true, true>), dim3(grid), dim3(threads), lds, s, dev, host.n, tile);  \
+    hipLaunchKernelGGL((KER<true, true>), dim3(grid), dim3(256), lds, s, dev, host.n, tile);  \
   else if (host.aligned)                                                                      \
-    hipLaunchKernelGGL((KER<true, false>), dim3(grid), dim3(threads), lds, s, dev, host.n, tile); \
+    hipLaunchKernelGGL((KER<true, false>), dim3(grid), dim3(256), lds, s, dev, host.n, tile); \
   else if (stream)                                                                            \
-    hipLaunchKernelGGL((KER<false, true>), dim3(grid), dim3(threads), lds, s, dev, host.n, tile); \
+    hipLaunchKernelGGL((KER<false, true>), dim3(grid), dim3(256), lds, s, dev, host.n, tile); \
   else                                                                                        \
-    hipLaunchKernelGGL((KER<false, false>), dim3(grid), dim3(threads), lds, s, dev, host.n, tile);
+    hipLaunchKernelGGL((KER<false, false>), dim3(grid), dim3(256), lds, s, dev, host.n, tile);
   if (to_soa) {
     SOAX_XPOSE(aos_to_soa_kernel)
   } else {
