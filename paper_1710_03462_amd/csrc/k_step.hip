@@ -26,10 +26,6 @@ namespace soax {
 
 namespace {
 
-constexpr int kLdsBudget = 48 * 1024;  // bytes of LDS staging per workgroup
-
-
-
 // ------------------------------------------------------------ SoA step
 
 // Loads and stores of the SoA step.  STREAM (the step's arrays far exceed
@@ -411,41 +407,6 @@ __global__ __launch_bounds__(1024) void aos_naive_kernel(AosStepArgs a) {
   update_record<INTEG, PT, VT, ALIGNED, TIER>(a.aos + i * a.stride, a, a.abc);
 }
 
-// Records per tile, and *block, the threads, of the LDS-staged step (block 0:
-// the default).  A caller's block takes one record per thread, as does the
-// default of 256 for sets that stay in the caches, for packed records and for
-// RK4.  Streaming sets of aligned records run faster the fewer 16-byte chunks
-// a thread moves, which spreads a tile over more waves and lets its traffic
-// leave and arrive in smaller pieces: one chunk per thread for the Euler
-// steps, about two for RK2 and Heun, whose arithmetic is one record per
-// thread.  us per step, 256 records and threads -> this rule, about 3.2 GB of
-// records: Euler 24-byte records 778 -> 743, 32 1052 -> 946, 48 1105 -> 992,
-// 64 1093 -> 945, 80 1154 -> 1099, 96 1162 -> 995, 112 1166 -> 1064, 160 1173
-// -> 1104; RK2 56 972 -> 903, 64 1049 -> 963, 80 1119 -> 1051, 112 1142 ->
-// 1070, 160 1158 -> 1108, but 40 1065 -> 1160, and 48 level at 1e8 records and
-// 4% slower at 3e6, so not below 56.  Between 128 and 512 MB of records (the
-// Infinity Cache holds 256) the larger records gain nothing (80 bytes, 160 MB:
-// 1% slower), so there only the small ones take it.
-template <int INTEG>
-int aos_shape(bool aligned, const AosStepArgs& a, int* block) {
-  const int64_t bytes = a.n * a.stride;
-  const bool beyond_caches = bytes >= 4 * kStreamBytes;
-  if (*block == 0 && aligned && bytes >= kStreamBytes) {
-    if (!field_integrator(INTEG) && a.stride <= (beyond_caches ? 256 : 64)) {
-      const int tile = a.stride <= 24 ? 128 : (a.stride <= 64 ? 64 : 32);
-      *block = (tile * a.stride / 16 + 63) / 64 * 64;
-      return tile;
-    }
-    if (field_integrator(INTEG) && INTEG != kRk4Abc && beyond_caches && a.stride >= 56 &&
-        a.stride <= 256) {
-      *block = a.stride <= 64 ? 128 : 192;
-      return 64;
-    }
-  }
-  if (*block == 0) *block = 256;
-  return aos_tile_records(a.stride, *block);
-}
-
 template <int INTEG, typename PT, typename VT, int TIER>
 hipError_t aos_step_launch(bool aligned, bool naive, int block, const AosStepArgs& a,
                            hipStream_t s) {
@@ -458,7 +419,7 @@ hipError_t aos_step_launch(bool aligned, bool naive, int block, const AosStepArg
       hipLaunchKernelGGL((aos_naive_kernel<INTEG, PT, VT, false, TIER>), dim3(grid), dim3(block),
                          0, s, a);
   } else {
-    const int tile = aos_shape<INTEG>(aligned, a, &block);
+    const int tile = aos_shape(INTEG, aligned, a.n, a.stride, &block);
     const int64_t grid = (a.n + tile - 1) / tile;
     const size_t lds = (static_cast<size_t>(tile) * a.stride + 15) & ~static_cast<size_t>(15);
     const bool stream = a.n * a.stride >= kStreamBytes;
@@ -1001,14 +962,6 @@ hipError_t launch_soa_step(int integ, int pos_t, int vel_t, int vec, int block,
     default:
       return hipErrorInvalidValue;
   }
-}
-
-int aos_tile_records(int stride, int block) {
-  int tile = block;
-  const int cap = (kLdsBudget / stride) & ~15;
-  if (tile > cap) tile = cap;
-  if (tile < 16) tile = 16;
-  return tile;
 }
 
 static hipError_t aos_any(int integ, int pos_t, int vel_t, bool aligned, bool naive, int block,

@@ -122,8 +122,56 @@ hipError_t launch_aos_step(int integ, int pos_t, int vel_t, bool aligned, int bl
 // One thread per record, direct per-field global accesses.
 hipError_t launch_aos_naive(int integ, int pos_t, int vel_t, bool aligned, int block,
                             const AosStepArgs& a, hipStream_t s);
+
+constexpr int kLdsBudget = 48 * 1024;  // bytes of LDS staging per workgroup
+
 // Largest tile (records) whose LDS staging fits the per-block budget.
-int aos_tile_records(int stride, int block);
+inline int aos_tile_records(int stride, int block) {
+  int tile = block;
+  const int cap = (kLdsBudget / stride) & ~15;
+  if (tile > cap) tile = cap;
+  if (tile < 16) tile = 16;
+  return tile;
+}
+
+// Records per tile, and *block, the threads, of the LDS-staged step (block 0:
+// the default).  A caller's block takes one record per thread, as does the
+// default of 256 for sets that stay in the caches, for packed records and for
+// RK4.  Streaming sets of aligned records run faster the fewer 16-byte chunks
+// a thread moves, which spreads a tile over more waves and lets its traffic
+// leave and arrive in smaller pieces: one chunk per thread for the Euler
+// steps, about two for RK2 and Heun, whose arithmetic is one record per
+// thread.  us per step, 256 records and threads -> this rule, about 3.2 GB of
+// records: Euler 24-byte records 778 -> 743, 32 1052 -> 946, 48 1105 -> 992,
+// 64 1093 -> 945, 80 1154 -> 1099, 96 1162 -> 995, 112 1166 -> 1064, 160 1173
+// -> 1104; RK2 56 972 -> 903, 64 1049 -> 963, 80 1119 -> 1051, 112 1142 ->
+// 1070, 160 1158 -> 1108, but 40 1065 -> 1160, and 48 level at 1e8 records and
+// 4% slower at 3e6, so not below 56.  Between 128 and 512 MB of records (the
+// Infinity Cache holds 256) the larger records gain nothing (80 bytes, 160 MB:
+// 1% slower), so there only the small ones take it.  A launch holds fewer than
+// 2^32 threads: one chunk per thread reaches that at 69 GB of records, from
+// where on one record per thread is taken again.
+inline int aos_shape(int integ, bool aligned, int64_t n, int stride, int* block) {
+  const int64_t bytes = n * stride;
+  const bool beyond_caches = bytes >= 4 * kStreamBytes;
+  if (*block == 0 && aligned && bytes >= kStreamBytes) {
+    int tile = 0, threads = 0;
+    if (!field_integrator(integ) && stride <= (beyond_caches ? 256 : 64)) {
+      tile = stride <= 24 ? 128 : (stride <= 64 ? 64 : 32);
+      threads = (tile * stride / 16 + 63) / 64 * 64;
+    } else if (field_integrator(integ) && integ != kRk4Abc && beyond_caches && stride >= 56 &&
+               stride <= 256) {
+      tile = 64;
+      threads = stride <= 64 ? 128 : 192;
+    }
+    if (tile > 0 && (n + tile - 1) / tile * threads < (int64_t(1) << 32)) {
+      *block = threads;
+      return tile;
+    }
+  }
+  if (*block == 0) *block = 256;
+  return aos_tile_records(stride, *block);
+}
 
 // -------------------------------------------------------------- transposes
 
