@@ -329,6 +329,11 @@ soax_status soax_set_record(soax_set* set, int64_t i, const void* host_record);
  * it and drop the last", computed as: the flagged slots below n' = n - m
  * (m flagged particles) in ascending order receive the unflagged particles
  * at or above n' in descending order.  Writes n' to *new_n (host).
+ * The device memory that this call, soax_sqdist_loss and soax_adjoint need
+ * for themselves comes from buffers that the library keeps for the next such
+ * call until the process ends: at most 64 MB per device, whatever the number
+ * of sets, streams and threads; what does not fit there is released in stream
+ * order when the call is done.
  * Errors: ARG, HIP, OOM.
  */
 soax_status soax_remove_flagged(soax_set* set, const uint8_t* flags, int64_t* new_n, void* stream);

@@ -21,134 +21,6 @@ extern "C" {
 
 // ------------------------------------------------------------- adjoints
 
-// Device memory for the per-workgroup partial sums of one call, in stream
-// order.  Taking it from the stream's memory pool and giving it back costs up
-// to 25 us of host time (loss of 1000 particles 46 -> 14 us a call, adjoint 43
-// -> 15), so up to kKept buffers of kKeptBytes are kept per device.  A buffer
-// is handed out again to the stream that used it last, or to any stream once
-// the event recorded after its last use has completed; the stream waits for
-// that event in any case, so that a stream handle that has been destroyed and
-// given out anew is in order too.  Idle buffers beyond kIdle are given back.
-// Larger requests and capturing streams (whose memory must belong to the
-// graph) take the pool.
-namespace {
-
-// Querying or making an event would invalidate a capture that another thread
-// has open in the global mode; neither touches a capturing stream here.
-class RelaxedCapture {
- public:
-  RelaxedCapture() { on_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
-  ~RelaxedCapture() {
-    if (on_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
-  }
-  RelaxedCapture(const RelaxedCapture&) = delete;
-  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
-
- private:
-  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;  // the thread's own, once exchanged
-  bool on_;
-};
-
-constexpr int kMaxDevices = 64;
-
-class Partials {
- public:
-  Partials() = default;
-  Partials(const Partials&) = delete;
-  Partials& operator=(const Partials&) = delete;
-  ~Partials() { (void)release(); }
-  hipError_t take(size_t bytes, hipStream_t s);
-  hipError_t release();  // after the last launch that uses it
-  double* get() const { return static_cast<double*>(p_); }
-
- private:
-  struct Buffer {
-    void* p;  // null: this place is free
-    hipEvent_t done;
-    hipStream_t last;
-    bool busy;
-  };
-  static constexpr size_t kKeptBytes = size_t(1) << 20;  // 1.1e7 particles
-  static constexpr int kKept = 8, kIdle = 2;
-  static std::mutex mu_;
-  static Buffer kept_[kMaxDevices][kKept];
-  void* p_ = nullptr;
-  hipStream_t s_ = nullptr;
-  Buffer* b_ = nullptr;
-};
-
-std::mutex Partials::mu_;
-Partials::Buffer Partials::kept_[kMaxDevices][Partials::kKept];
-
-hipError_t Partials::take(size_t bytes, hipStream_t s) {
-  s_ = s;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (bytes > kKeptBytes || dev >= kMaxDevices || hipStreamIsCapturing(s, &cap) != hipSuccess ||
-      cap != hipStreamCaptureStatusNone)
-    return hipMallocAsync(&p_, bytes, s);
-  RelaxedCapture relaxed;
-  std::lock_guard<std::mutex> lock(mu_);
-  Buffer* pick = nullptr;
-  Buffer* place = nullptr;  // free
-  Buffer* spare = nullptr;  // idle beyond kIdle
-  int idle = 0;
-  for (Buffer& b : kept_[dev]) {
-    if (!b.p) {
-      place = &b;
-    } else if (b.busy) {
-      continue;
-    } else if (b.last == s && !pick) {
-      pick = &b;
-    } else if (hipEventQuery(b.done) == hipSuccess) {
-      if (!pick) pick = &b;
-      else if (++idle > kIdle) spare = &b;
-    }
-  }
-  (void)hipGetLastError();  // an event that is not ready is no error here
-  if (spare) {
-    (void)hipFreeAsync(spare->p, s);  // its last use has completed
-    (void)hipEventDestroy(spare->done);
-    *spare = Buffer{};
-  }
-  if (pick) {
-    if ((e = hipStreamWaitEvent(s, pick->done, 0)) != hipSuccess) return e;
-  } else {
-    if (!place) return hipMallocAsync(&p_, bytes, s);
-    Buffer b{nullptr, nullptr, s, false};
-    if ((e = hipMallocAsync(&b.p, kKeptBytes, s)) != hipSuccess) return e;
-    if ((e = hipEventCreateWithFlags(&b.done, hipEventDisableTiming)) != hipSuccess) {
-      (void)hipFreeAsync(b.p, s);
-      return e;
-    }
-    pick = place;
-    *pick = b;
-  }
-  pick->busy = true;
-  b_ = pick;
-  p_ = pick->p;
-  return hipSuccess;
-}
-
-hipError_t Partials::release() {
-  hipError_t e = hipSuccess;
-  if (b_) {
-    std::lock_guard<std::mutex> lock(mu_);
-    e = hipEventRecord(b_->done, s_);
-    b_->last = s_;
-    b_->busy = false;
-  } else if (p_) {
-    e = hipFreeAsync(p_, s_);
-  }
-  b_ = nullptr;
-  p_ = nullptr;
-  return e;
-}
-
-}  // namespace
-
 static soax_status check_abc_host(const double* abc) {
   if (!abc) return fail(SOAX_E_ARG, "abc is NULL");
   if (!is_finite(abc[0]) || !is_finite(abc[1]) || !is_finite(abc[2]))
@@ -222,7 +94,7 @@ soax_status soax_adjoint_strided(const double* tape, const double* const* lamT, 
   hipStream_t s = as_stream(stream);
   const int tier = shift_tier(dt, abc[0], abc[1], abc[2]);
   const int64_t parts = std::max<int64_t>(adjoint_partials(n, tier), 1);
-  Partials partial;
+  DeviceScratch partial;
   hipError_t e = partial.take(parts * 3 * sizeof(double), s);
   if (e != hipSuccess) return fail(SOAX_E_OOM, "device memory for partial sums: %s", hipGetErrorString(e));
   AdjointArgs a{};
@@ -231,7 +103,7 @@ soax_status soax_adjoint_strided(const double* tape, const double* const* lamT, 
     a.lam[d] = lamT[d];
     a.gx[d] = grad_x0[d];
   }
-  a.partial = partial.get();
+  a.partial = static_cast<double*>(partial.get());
   a.grad_abc = grad_abc;
   a.stride = stride;
   a.n = n;
@@ -362,7 +234,7 @@ static soax_status sqdist_impl(const double* const* xT, int64_t stride,
   if (n < 0 || n > kMaxParticles) return fail(n < 0 ? SOAX_E_ARG : SOAX_E_RANGE, "bad n");
   hipStream_t s = as_stream(stream);
   const int64_t parts = std::max<int64_t>(loss_partials(n), 1);
-  Partials partial;
+  DeviceScratch partial;
   hipError_t e = partial.take(parts * 3 * sizeof(double), s);
   if (e != hipSuccess) return fail(SOAX_E_OOM, "device memory for partial sums: %s", hipGetErrorString(e));
   LossArgs a{};
@@ -371,7 +243,7 @@ static soax_status sqdist_impl(const double* const* xT, int64_t stride,
     a.target[d] = target[d];
     a.lam[d] = lamT ? lamT[d] : nullptr;
   }
-  a.partial = partial.get();
+  a.partial = static_cast<double*>(partial.get());
   a.loss = loss;
   a.stride = stride;
   a.n = n;

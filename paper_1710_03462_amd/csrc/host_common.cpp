@@ -13,6 +13,22 @@ namespace host {
 
 namespace {
 thread_local std::string g_last_error;
+
+// Querying or making an event would invalidate a capture that another thread
+// has open in the global mode; neither touches a capturing stream here.
+class RelaxedCapture {
+ public:
+  RelaxedCapture() { on_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+  ~RelaxedCapture() {
+    if (on_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;  // the thread's own, once exchanged
+  bool on_;
+};
 }  // namespace
 
 soax_status fail(soax_status st, const char* fmt, ...) {
@@ -175,12 +191,88 @@ soax_status alloc_owned(const Layout& L, int64_t cap, void** soa_block, std::vec
   return SOAX_OK;
 }
 
+std::mutex DeviceScratch::mu_;
+DeviceScratch::Buffer DeviceScratch::kept_[kMaxDevices][DeviceScratch::kKept];
+
+hipError_t DeviceScratch::take(size_t bytes, hipStream_t s) {
+  s_ = s;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (bytes > kMaxBytes || dev >= kMaxDevices || hipStreamIsCapturing(s, &cap) != hipSuccess ||
+      cap != hipStreamCaptureStatusNone)
+    return hipMallocAsync(&p_, bytes, s);
+  RelaxedCapture relaxed;
+  std::lock_guard<std::mutex> lock(mu_);
+  Buffer* pick = nullptr;   // the smallest that fits
+  bool pick_done = false;   // its last use has completed
+  Buffer* place = nullptr;  // free
+  Buffer* spare = nullptr;  // the smallest other idle one
+  size_t total = 0;
+  int idle = 0;
+  for (Buffer& b : kept_[dev]) {
+    total += b.bytes;
+    if (!b.p) {
+      place = &b;
+      continue;
+    }
+    if (b.busy) continue;
+    const bool done = hipEventQuery(b.done) == hipSuccess;
+    if ((done || b.last == s) && b.bytes >= bytes && !(pick && pick->bytes <= b.bytes)) {
+      pick = &b;
+      pick_done = done;
+    } else if (done) {
+      ++idle;
+      if (!spare || b.bytes < spare->bytes) spare = &b;
+    }
+  }
+  (void)hipGetLastError();  // an event that is not ready is no error here
+  if (idle > kIdle) {
+    total -= spare->bytes;
+    (void)hipFreeAsync(spare->p, s);  // its last use has completed
+    (void)hipEventDestroy(spare->done);
+    *spare = Buffer{};
+  }
+  if (pick) {
+    if (!pick_done && (e = hipStreamWaitEvent(s, pick->done, 0)) != hipSuccess) return e;
+  } else {
+    Buffer b{nullptr, kMinBytes, nullptr, s, false};
+    while (b.bytes < bytes) b.bytes *= 2;
+    if (!place || total + b.bytes > kTotalBytes) return hipMallocAsync(&p_, bytes, s);
+    if ((e = hipMallocAsync(&b.p, b.bytes, s)) != hipSuccess) return e;
+    if ((e = hipEventCreateWithFlags(&b.done, hipEventDisableTiming)) != hipSuccess) {
+      (void)hipFreeAsync(b.p, s);
+      return e;
+    }
+    pick = place;
+    *pick = b;
+  }
+  pick->busy = true;
+  b_ = pick;
+  p_ = pick->p;
+  return hipSuccess;
+}
+
+hipError_t DeviceScratch::release() {
+  hipError_t e = hipSuccess;
+  if (b_) {
+    std::lock_guard<std::mutex> lock(mu_);
+    e = hipEventRecord(b_->done, s_);
+    b_->last = s_;
+    b_->busy = false;
+  } else if (p_) {
+    e = hipFreeAsync(p_, s_);
+  }
+  b_ = nullptr;
+  p_ = nullptr;
+  return e;
+}
+
 void free_set(soax_set* s) {
   if (!s) return;
   if (s->aosoa_dev) (void)hipFree(s->aosoa_dev);
   if (s->pinned_count) (void)hipHostFree(s->pinned_count);
-  for (void* p : s->scratch)
-    if (p) (void)hipFree(p);
   if (s->xpose_dev) (void)hipFree(s->xpose_dev);
   if (s->owned_soa) (void)hipFree(s->owned_soa);
   if (s->owned_aos) (void)hipFree(s->owned_aos);

@@ -95,29 +95,6 @@ struct DevBuf {  // stream-ordered scratch, released on the same stream
   }
 };
 
-// Scratch `which` of the set, at least `bytes`: the buffer the set keeps
-// (allocating and releasing it on each call costs about 10 us of host time),
-// or, beyond kKeptScratch, `own`, released when the call ends.
-hipError_t set_scratch(soax_set* set, int which, size_t bytes, hipStream_t s, DevBuf& own,
-                       void** p) {
-  if (bytes > kKeptScratch) {
-    const hipError_t e = own.alloc(bytes, s);
-    *p = own.p;
-    return e;
-  }
-  if (set->scratch_bytes[which] < bytes) {
-    if (set->scratch[which]) (void)hipFreeAsync(set->scratch[which], s);
-    set->scratch[which] = nullptr;
-    set->scratch_bytes[which] = 0;
-    const size_t size = std::min(kKeptScratch, 2 * bytes);
-    const hipError_t e = hipMallocAsync(&set->scratch[which], size, s);
-    if (e != hipSuccess) return e;
-    set->scratch_bytes[which] = size;
-  }
-  *p = set->scratch[which];
-  return hipSuccess;
-}
-
 }  // namespace
 
 extern "C" {
@@ -280,11 +257,16 @@ soax_status soax_remove_flagged(soax_set* set, const uint8_t* flags, int64_t* ne
     HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&set->pinned_count), sizeof(int32_t),
                           hipHostMallocDefault),
             "hipHostMalloc");
-  DevBuf own_table, own_lists;
-  void* table = nullptr;  // tile counts and their exclusive sums
-  HIP_TRY(set_scratch(set, 0, 2 * tiles * sizeof(int32_t), s, own_table, &table),
-          "hipMallocAsync(counts)");
-  int32_t* counts = static_cast<int32_t*>(table);
+  // Tile counts and their exclusive sums, then the lists of moves: n / 2 moves
+  // at most, or as many as a kept buffer has room for beside the counts.  More
+  // than that take memory of their own once their number is known (4.1e6
+  // moves and more; a second buffer on every call costs 4 to 8 us).
+  DeviceScratch table, more;
+  const size_t table_bytes = (2 * tiles * sizeof(int32_t) + 15) & ~size_t(15);
+  const size_t list_bytes =
+      std::min((2 * (n / 2) + 1) * sizeof(int32_t), DeviceScratch::kMaxBytes - table_bytes);
+  HIP_TRY(table.take(table_bytes + list_bytes, s), "device memory for the counts and lists");
+  int32_t* counts = static_cast<int32_t*>(table.get());
   int32_t* before = counts + tiles;
   HIP_TRY(launch_count_flags(flags, n, counts, before, set->pinned_count, s),
           "flag count launch");
@@ -308,10 +290,11 @@ soax_status soax_remove_flagged(soax_set* set, const uint8_t* flags, int64_t* ne
       mv.record_stride = static_cast<int32_t>(set->L.stride);
       mv.record_word = record_word(set);
     }
-    void* lists = nullptr;
-    HIP_TRY(set_scratch(set, 1, (2 * moves_max + 1) * sizeof(int32_t), s, own_lists, &lists),
-            "hipMallocAsync(lists)");
-    int32_t* hole_at = static_cast<int32_t*>(lists);
+    const size_t need = (2 * moves_max + 1) * sizeof(int32_t);
+    if (need > list_bytes) HIP_TRY(more.take(need, s), "device memory for the lists");
+    int32_t* hole_at = need > list_bytes
+                           ? static_cast<int32_t*>(more.get())
+                           : reinterpret_cast<int32_t*>(static_cast<char*>(table.get()) + table_bytes);
     int32_t* mover_at = hole_at + moves_max;
     int32_t* nmoves = mover_at + moves_max;
     HIP_TRY(launch_rank_flags(flags, n, n_new, before, hole_at, mover_at, nmoves, s),

@@ -16,8 +16,8 @@
 // 64-byte stores to the same places 104 us, with the read that would need
 // 397 us).  Removing 1% of 1e8 particles from both copies, with the resize
 // before it: 633 us when the host summed the counts and every array had its
-// own zero fill, 484 us now, of which the moves take 320 to 355; from a set of
-// 1000 particles 149 us before, 50 us now.
+// own zero fill, 487 us now, of which the moves take 320 to 355; from a set of
+// 1000 particles 150 us before, 45 us now.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
