@@ -22,10 +22,16 @@ NUMPY_DTYPE = {"i8": np.int8, "u8": np.uint8, "i32": np.int32, "i64": np.int64,
 MAX_PARTICLES = 2 ** 31 - 1  # records a set can hold (the C ABI's limit)
 
 
+# torch's own shortcut to the handle (0.3 us in place of 2.8 us of every call,
+# no torch.cuda.Stream object); not a public name, so it may be absent.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_handle():
-    """The current stream's handle as an integer, without a torch.cuda.Stream
-    object (0.3 us in place of 2.8 us of every call)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """The current stream's handle as an integer."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def current_stream():
