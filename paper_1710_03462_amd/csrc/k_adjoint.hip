@@ -266,10 +266,13 @@ struct KeptTrig {
   }
 };
 
-// States of a 20-state segment kept in LDS: 6 x 48 bytes for each of the two
-// workgroups of 256 threads that share a compute unit (147 of its 160 KB);
-// the others' 168 registers leave two waves per SIMD.
+// States of a 20-state segment kept in LDS: 6 x 48 bytes a thread, and 24 for
+// block_sum3, for each of the two workgroups of 256 threads that share a
+// compute unit (156 of its 160 KB); the others' 168 registers leave two waves
+// per SIMD.
 constexpr int kLdsStates = 6;
+static_assert(2 * kRedBlock * (kLdsStates * sizeof(Trig3) + 3 * sizeof(double)) <= 160 * 1024,
+              "two workgroups must share a compute unit's LDS");
 
 // The adjoint for any k and nsteps (shifts of at most 1/8).  4e6 particles x
 // 160 steps, forward and loss included, before -> now: k = 16 7.28 -> 5.71 ms,
