@@ -111,7 +111,7 @@ soax_status soax_adjoint_strided(const double* tape, const double* const* lamT, 
   a.k = k;
   a.dt = dt;
   a.step = step_abc(AbcParams{abc[0], abc[1], abc[2]}, dt);
-  a.tier = shift_tier(dt, abc[0], abc[1], abc[2]);
+  a.tier = tier;
   e = launch_adjoint(a, s);
   const hipError_t e2 = partial.release();
   if (e != hipSuccess) return hip_fail(e, "adjoint launch");
@@ -128,8 +128,9 @@ soax_status soax_adjoint(const double* tape, const double* const* lamT, int64_t 
 // ------------------------------------------- allocation-free adjoint
 
 // Device memory of soax_adjoint_noalloc: the adjoint kernel's per-workgroup
-// partial sums of dL/d(A,B,C), three doubles per workgroup of 256 particles,
-// in a fixed array that every GPU the library runs on holds until the
+// partial sums of dL/d(A,B,C), three doubles per workgroup of 256 particles
+// (of 64 in sets of at most 2^15, which need less than the limit's share), in
+// a fixed array that every GPU the library runs on holds until the
 // process ends.  Host code never passes `scratch` itself to a kernel (on
 // the host the name stands for a host-side symbol, not a device address):
 // it passes the address hipGetSymbolAddress returns for the current device.
@@ -157,7 +158,8 @@ static soax_status scratch_ptr(double** out) {
   return SOAX_OK;
 }
 
-// Particles whose partial sums fit the scratch: one triple per workgroup.
+// Particles whose partial sums fit the scratch: one triple per workgroup of
+// kAdjointBlock.
 static_assert(SOAX_ADJOINT_NOALLOC_MAX_N ==
                   kNoAllocScratchBytes / (3 * int64_t(sizeof(double))) * kAdjointBlock,
               "the header's limit must match the scratch size");
