@@ -1,10 +1,14 @@
 // device_math.h -- per-particle arithmetic shared by every kernel of the
 // library: the periodic wrap, the ABC field and one explicit-midpoint step.
 //
-// Every expression is written as separate IEEE operations; the library is
+// The Euler steps and the wrap are separate IEEE operations; the library is
 // compiled with -ffp-contract=off so that x + dt*v is a multiply and an add,
-// never an FMA (eq. (1) of Section 2 evaluated as written).  Only the sine
-// and cosine evaluations (trig.h) use fused multiply-adds, explicitly.
+// never an FMA (eq. (1) of Section 2 evaluated as written).  Where something
+// is fused, the source says so: the field's components, the sums of RK4's
+// stages, the sines and cosines (trig.h) and the adjoint (k_adjoint.hip) are
+// chains of explicit fused multiply-adds, and the field integrators take dt/2
+// and dt folded into the amplitudes (StepAbc), in the order that their
+// functions below write out.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -3,8 +3,9 @@
 // recomputation, and a squared-distance loss.
 //
 // One thread owns one particle (in small sets a quad of lanes does, see below)
-// for the whole time loop; the state stays in registers.  The adjoint walks the checkpoint segments backwards; for each
-// segment it recomputes the states from the checkpoint, keeping every state's
+// for the whole time loop; the state stays in registers.  The adjoint walks
+// the checkpoint segments backwards; for each segment it recomputes the states
+// from the checkpoint, keeping every state's
 // sines and cosines (in registers, indexed by compile-time constants through
 // fully unrolled loops so that they never touch scratch memory, and in LDS),
 // and sweeps them backwards.  Segments longer than what is kept are split

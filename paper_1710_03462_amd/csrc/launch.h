@@ -51,18 +51,19 @@ inline StepAbc step_abc(const AbcParams& p, double dt) {
 }
 
 // Largest displacement per coordinate for which a step's midpoint and end
-// point sines come from its start point by angle addition without a check.
+// point sines come from its start point by rotation without a check.
 constexpr double kShiftLimit = 1.0 / 64;
 
 // What the host proves about every displacement of a step of the field
-// integrators (the shift of the angle additions): kTierSmall, every shift at
-// most kShiftLimit (the short series); kTierMid, every shift at most 1/8 (the
-// longer series; checked against kShiftMidLimit, 1/8 less 2^-20 of it, so
-// that no rounding of dt u can carry a shift past 1/8); kTierAny, no bound.
-// The tier is a function of dt and the amplitudes alone, so every layout, the
+// integrators (the angles of the rotations): kTierSmall, every shift at most
+// kShiftLimit (the short polynomials); kTierMid, every shift at most 1/8 (the
+// longer ones; checked against kShiftMidLimit, 1/8 less 2^-20 of it, so that
+// no rounding of dt u can carry a shift past 1/8); kTierAny, no bound.  The
+// tier is a function of dt and the amplitudes alone, so every layout, the
 // batch and the single-set kernels take the same one for the same step; the
-// mid-tier kernels give exactly the results of the kTierAny kernels on every
-// step that satisfies their bound.
+// mid-tier steps give exactly the results of the kTierAny ones on every step
+// that satisfies their bound.  (The loops over many steps of k_adjoint.hip
+// carry sines and cosines from state to state in both bounded tiers.)
 enum ShiftTier : int32_t { kTierSmall = 0, kTierMid = 1, kTierAny = 2 };
 constexpr double kShiftMidLimit = 0.125 * (1.0 - 0x1p-20);
 
